@@ -334,14 +334,16 @@ class MatrixStep:
         surv = int(self.saved.count.item())
         g_reads = 8 if self.self_pairs else 4  # the entry's g (and its transpose's)
         if kernel == "k_matrix_cull":
-            return ("hbm", 4 * self.pairs + box * boxes,
-                    f"4 B of output per pair x {self.pairs} pairs + {box} B x {boxes} boxes")
+            return "hbm", self.pairs // 8 + box * boxes, (f"1 mask bit per pair x {self.pairs} + "
+                                                          f"{box} B x {boxes} boxes")
         if kernel == "k_matrix_exact":
             return ("hbm", 21 * surv + box * boxes,
                     f"21 B per survivor (8 id + 4 IoU + 1 nx + 8 flags) x {surv} + "
                     f"{box} B x {boxes} boxes")
-        if kernel == "k_matrix_fill":
-            return "hbm", 8 * surv, f"8 B pair id per survivor x {surv}"
+        if kernel == "k_matrix_list":
+            return ("hbm", 4 * self.pairs + self.pairs // 8 + 8 * surv,
+                    f"4 B of output and 1 mask bit per pair x {self.pairs} + 8 B pair id per "
+                    f"survivor x {surv}")
         if kernel == "k_matrix_bwd":
             per = 17 + g_reads
             return ("hbm", per * surv + 2 * box * boxes,

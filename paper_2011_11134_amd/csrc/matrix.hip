@@ -2,25 +2,25 @@
 // such as per-scene self-pairs of 3D boxes, Sec. IV-A case study at scale) and
 // their backward from the saved per-pair state (Sec. II-B: nx and xflags).
 //
-// The forward is split by register pressure into lean cull kernels and one
-// dense exact kernel, with no shared counter anywhere:
-//   k_matrix_cull -- one wavefront per tile of R rows x 2048 / R columns of
-//     one segment (R = 4, 8 or 16, chosen per call: the autotuner weighs
-//     longer contiguous output rows against more column-bound loads per
-//     pair).  The rows' axis-aligned bounds (and z-extents)
-//     sit in scalar registers; each lane bounds its column boxes 64 at a
-//     time, tests them against the rows, writes every pair's initial value
-//     (0, or the self diagonal's 1) straight to the output row segments
-//     (coalesced), and records the tile's survivor mask and count.
-//   k_scan_totals, k_scan_apply -- exclusive prefix of the tile counts in two
-//     parallel passes (k_scan_small: in one workgroup, for at most 8192
-//     tiles), so the work list is laid out tile by tile, deterministically.
-//   k_matrix_fill -- reads the masks; survivors go to their tile's range.
+// The forward is split by register pressure into lean cull and list kernels
+// and one dense exact kernel, with no shared counter anywhere:
+//   k_matrix_cull -- survivor masks and counts per tile of R rows x 2048 / R
+//     columns of one segment (R = 4, 8 or 16, chosen per call).  A lane holds a
+//     row; the pairs it tests are those whose bins on every axis overlap, found
+//     64 columns at a time from bit sets in LDS.
+//   k_matrix_list -- lays the work list out tile by tile, deterministically
+//     (the prefix of the tile counts, then the masks' survivors), while its
+//     other workgroups write the output's zeros as a flat stream.
 //   k_matrix_exact -- one lane per survivor with every lane busy: the exact
 //     pair forward, the IoU written to its place in the output, nx / xflags
-//     kept in the work list for the backward.
-// A persistent grid walks the tiles of all segments (a prefix sum of tiles per
-// segment computed on the device by k_seg_prep, so everything is
+//     kept in the work list for the backward; and the self diagonal's 1s.
+// (k_scan_totals sums chunks of tile counts first where the table is too
+// large for each list workgroup to sum the counts before its own.)
+// c5 (64 scenes, 93.6 M pairs) takes 20 + 62 + 36 us; a kernel that tested every
+// pair and wrote the tiles' values (103 us), two scan passes (11), a fill of
+// the list (13) and the exact pass (31) took 162 with the segments' prefixes.
+// Grids walk the units or tiles of all segments, whose sizes are on the
+// device (the prefixes over segments are computed there, so everything is
 // graph-capturable).  The backward (k_matrix_bwd) gives one wavefront a row
 // group of 8 rows, whatever the tile shape: the entries of the tile rows
 // that cover it are one contiguous range of the work list; each step's row
@@ -45,6 +45,11 @@ constexpr int kTilePairs = DGAL_TILE_PAIRS;
 constexpr int kGroupRows = 8;     // rows of a backward row group
 constexpr int kCullBlock = 256;   // four independent wavefronts
 constexpr int kScanBlock = 1024;
+constexpr int kListBlock = 256;
+constexpr int kListTiles = kListBlock;  // tiles of a list step
+constexpr int kFillSegBlocks = 2048;    // workgroups that fill blocks with gaps between them
+// tables of up to this many tiles are summed by the list pass itself
+constexpr int64_t kListDirect = 65536;
 constexpr int kExactBlock = 256;
 constexpr int kMaxSeg = DGAL_MAX_SEGMENTS;
 static_assert(kTilePairs == 2048, "32 words of survivor bits per tile");
@@ -66,8 +71,8 @@ struct SegArgs {
   int nseg;
   int64_t a_count, b_count, out_size;
   int self_pairs;
-  const int64_t* tile_prefix;   // [nseg+1] (segmented), from k_seg_prep
-  const int64_t* group_prefix;  // [nseg+1] row groups (segmented), from k_seg_prep
+  const int64_t* tile_prefix;   // [nseg+1] (segmented), from the cull pass or k_seg_prep
+  const int64_t* group_prefix;  // [nseg+1] row groups (segmented), likewise
   int rows_log2;                // tiles of 2^rows_log2 rows x 2^(11 - rows_log2) columns
 };
 
@@ -112,8 +117,9 @@ __device__ __forceinline__ int64_t col_tiles_of(const Segment& g, int rl) {
   return (g.nb + (1 << cl) - 1) >> cl;
 }
 
-// Tile and row-group prefixes over segments (one workgroup).  Rejected
-// segments own nothing and raise kErrSegment.
+// Tile and row-group prefixes over segments (one workgroup), for a backward
+// whose forward did not keep them.  Rejected segments own nothing and raise
+// kErrSegment.
 __global__ __launch_bounds__(256) void k_seg_prep(SegArgs a, int* err, int64_t* tile_prefix,
                                                   int64_t* group_prefix) {
   __shared__ int64_t part_t[256], part_g[256];
@@ -225,14 +231,12 @@ __device__ __forceinline__ void wave_sync() {
 struct CullArgs {
   SegArgs seg;
   PolyArgs a, b;
-  int64_t single_tiles;
-  float* iou;
-  int64_t* pair_id;
-  int64_t capacity;
-  int64_t* tile_start;
+  int64_t single_units;  // one block: its units
   int32_t* tile_count;
   int64_t tile_capacity;
   uint64_t* tile_mask;  // [tile_capacity][kMaskWords]
+  int64_t* tile_prefix;   // [nseg+1] (segmented), written for the later kernels
+  int64_t* group_prefix;  // [nseg+1]
   int* err;
 };
 
@@ -240,49 +244,10 @@ constexpr int kBitWords = kTilePairs / 64;  // survivor bits of a tile
 constexpr int kMaskWords = DGAL_TILE_MASK_WORDS;            // + tile origin + row length
 static_assert(kMaskWords == kBitWords + 2 && kMaskWords <= 64, "mask words");
 
-// Segment s without the checks of load_segment: the tile walk only reaches
-// segments that k_seg_prep accepted.
-__device__ __forceinline__ Segment tile_segment(const SegArgs& a, int s) {
-  Segment g;
-  if (a.a_off == nullptr) {
-    g.a0 = 0;
-    g.b0 = 0;
-    g.na = a.a_count;
-    g.nb = a.b_count;
-    g.out0 = 0;
-  } else {
-    g.a0 = a.a_off[s];
-    g.b0 = a.b_off[s];
-    g.na = a.a_off[s + 1] - g.a0;
-    g.nb = a.b_off[s + 1] - g.b0;
-    g.out0 = a.out_off[s];
-  }
-  g.ok = true;
-  return g;
-}
-
 // Sign bit of the difference hi - lo: set when lo > hi, clear when they are
 // equal (the closed test keeps touching boxes).
 __device__ __forceinline__ uint32_t gap_bits(float hi, float lo) {
   return __float_as_uint(hi - lo);
-}
-
-template <int N, class F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>()), ...);
-}
-// f(0), f(1), ..., f(N - 1) with compile-time arguments.
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl<N>(f, std::make_integer_sequence<int, N>());
-}
-
-// v_writelane: `val` (wave-uniform) into lane L (a constant) of `old`.
-template <int L>
-__device__ __forceinline__ uint32_t write_lane(uint32_t old, uint32_t val) {
-  static_assert(L >= 0 && L < 64, "lane");
-  asm("v_writelane_b32 %0, %1, %2" : "+v"(old) : "s"(val), "n"(L));
-  return old;
 }
 
 // The largest float below v (finite v): lo < v <=> lo <= below(v), so the
@@ -293,242 +258,383 @@ __device__ __forceinline__ float below(float v) {
   return __uint_as_float((int32_t)b > 0 ? b - 1u : b + 1u);
 }
 
-// Walks a contiguous range of tiles: the segment is searched once, then
-// followed tile by tile (row-major within a segment, segments in order), so
-// that a tile costs no search and no division.
-template <int R>
-struct TileCursor {
-  static constexpr int C = kTilePairs / R;
-  static constexpr int RL = R == 4 ? 2 : (R == 8 ? 3 : 4);
-  int s;
-  int64_t seg_end;  // first tile past segment s
-  Segment g;
-  int64_t nct, tr, tc;
-
-  __device__ void load(const SegArgs& seg, bool segmented) {
-    g = tile_segment(seg, s);
-    nct = col_tiles_of(g, RL);
-    seg_end = segmented ? seg.tile_prefix[s + 1] : (int64_t)0x7fffffffffffffff;
-  }
-  __device__ void seek(const SegArgs& seg, bool segmented, int64_t u) {
-    s = segmented ? wave_find_segment(seg.tile_prefix, seg.nseg, u) : 0;
-    load(seg, segmented);
-    const int64_t lu = segmented ? u - seg.tile_prefix[s] : u;
-    tr = lu / nct;
-    tc = lu - tr * nct;
-  }
-  // to tile u + 1 (u the current tile)
-  __device__ void next(const SegArgs& seg, bool segmented, int64_t u) {
-    if (++tc == nct) {
-      tc = 0;
-      ++tr;
-    }
-    if (u + 1 >= seg_end) {  // the next non-empty segment
-      do {
-        ++s;
-      } while (s < seg.nseg && seg.tile_prefix[s + 1] <= u + 1);
-      if (s < seg.nseg) {
-        load(seg, segmented);
-        tr = 0;
-        tc = 0;
-      }
-    }
-  }
-  __device__ int64_t r0() const { return tr * R; }
-  __device__ int64_t cb() const { return tc * C; }
-};
-
-// The contiguous range of tiles of wavefront `wid` out of `nw`.
-__device__ __forceinline__ void wave_tiles(int64_t total, int64_t wid, int64_t nw, int64_t& u0,
-                                           int64_t& u1) {
-  const int64_t per = (total + nw - 1) / nw;
-  u0 = wid * per;
-  u1 = u0 + per < total ? u0 + per : total;
+__device__ __forceinline__ int64_t wave_first(int64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// Count pass: writes every pair of the tile (0 for the culled ones, which
-// stays, or 1 on the self diagonal; the exact kernel later overwrites the
-// survivors), the tile's survivor mask (kMaskWords words, chunk-major) and its
-// survivor count.  The tile walk is wave-uniform, so its indices, the segment
-// and the rows' bounds live in scalar registers.  The test of a (row, column)
-// pair is one OR of the sign bits of its four (2D) or six (3D) bound
-// differences, so that the vector unit does the work and the scalar unit only
-// counts: overlapping closed boxes (touching ones go to the exact kernel)
-// with overlapping open z extents (a closed test against upper ends lowered
-// by one ulp) survive; invalid columns and rows, and empty z extents, carry
-// x1 = -inf.
-template <int K, bool FIXED, bool Z3, int R>
-__global__ __launch_bounds__(kCullBlock) void k_matrix_cull(CullArgs m) {
-  constexpr int WAVES = kCullBlock / 64;
-  constexpr int C = kTilePairs / R;
-  static_assert(R == 4 || R == 8 || R == 16, "tile rows");
+// Quotient and remainder of a non-negative index by a positive divisor below
+// 2^24 (32-bit division when the index allows it).
+__device__ __forceinline__ void divmod(int64_t v, int64_t d, int64_t& q, int64_t& r) {
+  if (v < (int64_t)0xffffffff) {
+    const uint32_t q32 = (uint32_t)v / (uint32_t)d;
+    q = q32;
+  } else {
+    q = v / d;
+  }
+  r = v - q * d;
+}
+
+// ---- the cull pass ----------------------------------------------------
+// Survivor masks and counts, in units of kUnitRows rows x one tile column of
+// a segment.  The output's initial values are written by the list pass.
+constexpr int kUnitRows = kCullBlock;  // 64 rows a wavefront
+constexpr int kBins = 32;              // bins per axis of the masks' broad phase
+constexpr int kFillStep = 4 * kCullBlock;  // values a fill workgroup stores at once
+
+// The pass's work in one segment (none where the segment is rejected).
+__device__ __forceinline__ int64_t mask_units_of(const Segment& g, int rl) {
+  return (g.ok && g.na > 0 && g.nb > 0) ? (g.na + kUnitRows - 1) / kUnitRows * col_tiles_of(g, rl)
+                                        : 0;
+}
+__device__ __forceinline__ int64_t fill_units_of(const Segment& g, const float* iou) {
+  const int64_t mis = (int64_t)((reinterpret_cast<uintptr_t>(iou + g.out0) >> 2) & 3);
+  return (g.ok && g.na > 0 && g.nb > 0) ? (g.na * g.nb + mis + kFillStep - 1) / kFillStep : 0;
+}
+__device__ __forceinline__ int64_t tiles_of(const Segment& g, int rl) {
+  return g.ok ? tile_rows_of(g, rl) * col_tiles_of(g, rl) : 0;
+}
+
+// Exclusive prefixes over the segments of the workgroup's kind of units and
+// of the tiles: thread t holds those at segment t * per.  Computed by every
+// workgroup from the offsets (a few loads a thread), so that the pass needs
+// no launch before it and no workspace.
+struct SegScan {
+  int64_t units[kCullBlock], tiles[kCullBlock];
+  int64_t wave_sum[2][kCullBlock / 64];
+  int64_t total;  // units of all segments
+};
+
+template <class F>
+__device__ __forceinline__ void scan_segments(const SegArgs& a, SegScan& sc, F units_of) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int per = (a.nseg + kCullBlock - 1) / kCullBlock;
+  const int s0 = min(a.nseg, tid * per), s1 = min(a.nseg, s0 + per);
+  int64_t u = 0, t = 0;
+  for (int s = s0; s < s1; ++s) {
+    const Segment g = load_segment(a, s);
+    u += units_of(g);
+    t += tiles_of(g, a.rows_log2);
+  }
+  int64_t iu = u, it = t;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int64_t ou = __shfl_up(iu, d), ot = __shfl_up(it, d);
+    if (lane >= d) {
+      iu += ou;
+      it += ot;
+    }
+  }
+  if (lane == 63) {
+    sc.wave_sum[0][wave] = iu;
+    sc.wave_sum[1][wave] = it;
+  }
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) {
+    iu += sc.wave_sum[0][w];
+    it += sc.wave_sum[1][w];
+  }
+  sc.units[tid] = iu - u;
+  sc.tiles[tid] = it - t;
+  if (tid == kCullBlock - 1) sc.total = iu;
+  __syncthreads();
+}
+
+// The workgroup's second scan: the segments' tile and row-group prefixes for
+// the kernels that follow and for the backward; rejected segments own nothing
+// and raise kErrSegment.  After the tile prefixes (when there is room) goes the
+// size of the output, if the blocks cover it from 0 on without gaps, else -1.
+__device__ __forceinline__ void write_prefixes(const CullArgs& m, SegScan& sc) {
+  const SegArgs& a = m.seg;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int per = (a.nseg + kCullBlock - 1) / kCullBlock;
+  const int s0 = min(a.nseg, tid * per), s1 = min(a.nseg, s0 + per);
+  int64_t v = 0;
+  bool dense = true;
+  for (int s = s0; s < s1; ++s) {
+    const Segment g = load_segment(a, s);
+    if (g.ok) v += groups_of(g);
+    else atomicOr(m.err, kErrSegment);
+    const int64_t next = s + 1 < a.nseg ? a.out_off[s + 1] : g.out0 + g.na * g.nb;
+    dense = dense && g.ok && next == g.out0 + g.na * g.nb && (s > 0 || g.out0 == 0);
+  }
+  dense = __syncthreads_and(dense);
+  if (s0 < s1 && s1 == a.nseg && a.nseg < kMaxSeg) {
+    const Segment g = load_segment(a, a.nseg - 1);
+    m.tile_prefix[a.nseg + 1] = dense ? g.out0 + g.na * g.nb : -1;
+  }
+  int64_t rg = v;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int64_t o = __shfl_up(rg, d);
+    if (lane >= d) rg += o;
+  }
+  if (lane == 63) sc.wave_sum[0][wave] = rg;
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) rg += sc.wave_sum[0][w];
+  rg -= v;
+  int64_t rt = sc.tiles[tid];
+  if (tid == 0) {
+    m.tile_prefix[0] = 0;
+    m.group_prefix[0] = 0;
+  }
+  for (int s = s0; s < s1; ++s) {
+    const Segment g = load_segment(a, s);
+    if (g.ok) {
+      rg += groups_of(g);
+      rt += tiles_of(g, a.rows_log2);
+    }
+    m.tile_prefix[s + 1] = rt;
+    m.group_prefix[s + 1] = rg;
+  }
+}
+
+// Segment of unit u (u < total), its first unit and first tile.
+struct UnitSeg {
+  Segment g;
+  int64_t unit0, tile0;
+};
+
+template <class F>
+__device__ __forceinline__ UnitSeg find_unit(const SegArgs& a, const SegScan& sc, int64_t u,
+                                             F units_of) {
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool segmented = m.seg.a_off != nullptr;
-  const int64_t total = segmented ? m.seg.tile_prefix[m.seg.nseg] : m.single_tiles;
-
-  int64_t u0, u1;
-  wave_tiles(total, (int64_t)blockIdx.x * WAVES + wave, (int64_t)gridDim.x * WAVES, u0, u1);
-  TileCursor<R> cur;
-  if (u0 < u1) cur.seek(m.seg, segmented, u0);
-  // the rows' bounds, in scalar registers, kept while the tiles of a range
-  // stay in one tile row (the usual case: a range is a few tiles)
-  Bounds rb[R];
-  int64_t rows_of = -1;  // first row (in a) whose bounds rb holds
-  for (int64_t u = u0; u < u1; cur.next(m.seg, segmented, u), ++u) {
-    const Segment& g = cur.g;
-    const int64_t r0 = cur.r0(), cb = cur.cb();
-    const int nr = (int)min((int64_t)R, g.na - r0);
-    const int64_t ce = min(g.nb, cb + C);
-    float* out_rows = m.iou + g.out0 + r0 * g.nb;
-
-    if (g.a0 + r0 != rows_of) {  // uniform
-      // row bounds: lane j < nr bounds row j, then every lane holds all of them
-      rows_of = g.a0 + r0;
-      Bounds rl = {0.f, 0.f, -1.f, -1.f, 0.f, 0.f};
-      if (lane < nr) rl = box_bounds<K, FIXED, Z3>(m.a, g.a0 + r0 + lane);
-      if (lane >= nr || (Z3 && !(rl.hi > rl.lo))) rl.x1 = -__builtin_inff();
-      if (Z3) rl.hi = below(rl.hi);
+  // the last thread whose prefix is not past u
+  int k = -1;
 #pragma unroll
-      for (int j = 0; j < R; ++j) {
-        rb[j].x0 = lane_bcast(rl.x0, j);
-        rb[j].y0 = lane_bcast(rl.y0, j);
-        rb[j].x1 = lane_bcast(rl.x1, j);
-        rb[j].y1 = lane_bcast(rl.y1, j);
-        rb[j].lo = lane_bcast(rl.lo, j);
-        rb[j].hi = lane_bcast(rl.hi, j);
+  for (int q = 0; q < kCullBlock / 64; ++q)
+    k += __popcll(__ballot(sc.units[q * 64 + lane] <= u));
+  const int per = (a.nseg + kCullBlock - 1) / kCullBlock;
+  UnitSeg r;
+  r.unit0 = sc.units[k];
+  r.tile0 = sc.tiles[k];
+  const int s1 = min(a.nseg, k * per + per);
+  for (int s = k * per;; ++s) {
+    r.g = load_segment(a, s);
+    const int64_t n = units_of(r.g);
+    if (u < r.unit0 + n || s + 1 >= s1) break;
+    r.unit0 += n;
+    r.tile0 += tiles_of(r.g, a.rows_log2);
+  }
+  return r;
+}
+
+// Wave-wide minimum of v (every lane gets it), by data-parallel row moves.
+__device__ __forceinline__ float wave_min(float v) {
+#define DGAL_MIN_STEP(ctrl, rows)                                                            \
+  v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), \
+                                                          ctrl, rows, 0xf, false)))
+  DGAL_MIN_STEP(0x111, 0xf);  // row_shr:1, 2, 4, 8
+  DGAL_MIN_STEP(0x112, 0xf);
+  DGAL_MIN_STEP(0x114, 0xf);
+  DGAL_MIN_STEP(0x118, 0xf);
+  DGAL_MIN_STEP(0x142, 0xa);  // row_bcast:15 into rows 1 and 3
+  DGAL_MIN_STEP(0x143, 0xc);  // row_bcast:31 into rows 2 and 3
+#undef DGAL_MIN_STEP
+  return lane_bcast(v, 63);
+}
+
+// Inclusive prefix OR over the lanes of each half of the wavefront.
+__device__ __forceinline__ uint32_t half_prefix_or(uint32_t v) {
+#define DGAL_OR_STEP(ctrl, rows) \
+  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xf, false)
+  DGAL_OR_STEP(0x111, 0xf);
+  DGAL_OR_STEP(0x112, 0xf);
+  DGAL_OR_STEP(0x114, 0xf);
+  DGAL_OR_STEP(0x118, 0xf);
+  DGAL_OR_STEP(0x142, 0xa);
+#undef DGAL_OR_STEP
+  return v;
+}
+
+// Bin of a coordinate: monotone in v for any lo and scale (a NaN product, an
+// infinite scale times zero, counts as the lowest bin), so an order between
+// coordinates is an order between their bins.
+__device__ __forceinline__ int bin_of(float v, float lo, float scale) {
+  return (int)fminf(fmaxf((v - lo) * scale, 0.f), (float)(kBins - 1));
+}
+
+template <bool Z3, int C>
+struct MaskLds {
+  float4 xy[C];                         // the columns' bounds x0, y0, x1, y1
+  float2 z[Z3 ? C : 1];                 // and z-extents, the upper end lowered
+  // per axis and 64 columns: entry b < kBins holds the columns whose lower
+  // end lies in bin b or below, entry kBins + b those whose upper end lies
+  // in bin kBins - 1 - b or above
+  uint64_t bm[Z3 ? 3 : 2][C / 64][2 * kBins];
+};
+
+// Masks of one unit: kUnitRows rows from row r0 of segment g against the
+// columns of tile column tc; a lane holds a row.  A pair survives when its
+// closed boxes overlap (touching ones go to the exact kernel) and their open
+// z extents do (the closed test on upper ends lowered by one ulp): the sign
+// bits of its four (six) bound differences are all clear.  Only the pairs
+// whose bins overlap on every axis are tested: the columns' bins are kept as
+// bit sets, so that the two (three) axes cost a lane four (six) LDS reads for
+// 64 columns, and on c5 leave about one pair of them to test.  Bound by
+// latency (the LDS reads of the tests; the busiest lane has about four): 20 us
+// on c5, where testing every pair, 10 vector instructions for 64 pairs, took
+// 70 us without its stores; 5.5 us on 4096 x 4096.  Rows and columns
+// past the block, and empty z extents, survive nothing.
+template <int K, bool FIXED, bool Z3, int R>
+__device__ __forceinline__ void mask_unit(const CullArgs& m, const Segment& g, int64_t tile0,
+                                          int64_t r0, int64_t tc,
+                                          MaskLds<Z3, kTilePairs / R>& s) {
+  constexpr int C = kTilePairs / R, W = C / 64, D = Z3 ? 3 : 2, WAVES = kCullBlock / 64;
+  constexpr int RL = R == 4 ? 2 : (R == 8 ? 3 : 4);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t cb = tc * C;
+  const int nc = (int)min((int64_t)C, g.nb - cb);  // columns of the tile
+  __syncthreads();  // the previous unit's reads are done
+  for (int c = tid; c < C; c += kCullBlock) {
+    Bounds b = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (c < nc) b = box_bounds<K, FIXED, Z3>(m.b, g.b0 + cb + c);
+    if (Z3) {
+      if (c >= nc || !(b.hi > b.lo)) {
+        b.lo = __builtin_inff();  // marks a column that nothing meets
+        b.hi = 0.f;
+      }
+      s.z[c] = make_float2(b.lo, below(b.hi));
+    }
+    s.xy[c] = make_float4(b.x0, b.y0, b.x1, b.y1);
+  }
+  for (int i = tid; i < D * W * 2 * kBins; i += kCullBlock) (&s.bm[0][0][0])[i] = 0ull;
+  __syncthreads();
+  // the bins span the first 64 columns' bounds (others are clamped to them)
+  float lo[D], scale[D];
+  {
+    const bool in = lane < nc && !(Z3 && s.z[Z3 ? lane : 0].x == __builtin_inff());
+    const float4 b = s.xy[lane];
+    float2 z = make_float2(0.f, 0.f);
+    if constexpr (Z3) z = s.z[lane];
+    const float l[3] = {b.x, b.y, z.x}, h[3] = {b.z, b.w, z.y};
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      lo[a] = wave_min(in ? l[a] : __builtin_inff());
+      const float hi = -wave_min(in ? -h[a] : __builtin_inff());
+      scale[a] = (float)kBins * fast_rcp(hi - lo[a]);
+    }
+  }
+  for (int w = wave; w < W; w += WAVES) {  // each wavefront its own words
+    const int c = w * 64 + lane;
+    const float4 b = s.xy[c];
+    float2 z = make_float2(0.f, 0.f);
+    if constexpr (Z3) z = s.z[c];
+    const bool in = c < nc && !(Z3 && z.x == __builtin_inff());
+    const float l[3] = {b.x, b.y, z.x}, h[3] = {b.z, b.w, z.y};
+    const uint64_t bit = 1ull << lane;
+    if (in) {
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        __hip_atomic_fetch_or(&s.bm[a][w][bin_of(l[a], lo[a], scale[a])], bit, __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_or(&s.bm[a][w][2 * kBins - 1 - bin_of(h[a], lo[a], scale[a])], bit,
+                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
-    uint32_t n = 0;         // survivors so far (uniform; at most kTilePairs)
-    uint32_t mlo = 0u, mhi = 0u;  // lane w < kBitWords: mask word w of the tile
-    // the next 64 column boxes are loaded while the current ones are tested
-    Bounds nxt = {0.f, 0.f, -1.f, -1.f, 0.f, 0.f};
-    if (cb + lane < ce) nxt = box_bounds<K, FIXED, Z3>(m.b, g.b0 + cb + lane);
-    static_for<C / 64>([&](auto cic) {
-      constexpr int ci = decltype(cic)::value;
-      const int64_t c0 = cb + ci * 64;
-      if (c0 >= ce) return;  // uniform; so are the later chunks
-      const bool valid = c0 + lane < ce;
-      Bounds cbx = nxt;
-      if (c0 + 64 + lane < ce) nxt = box_bounds<K, FIXED, Z3>(m.b, g.b0 + c0 + 64 + lane);
-      if (!valid || (Z3 && !(cbx.hi > cbx.lo))) cbx.x1 = -__builtin_inff();
-      if (Z3) cbx.hi = below(cbx.hi);
-      // the self diagonal crosses this chunk at lane r0 + j - c0
-      const int64_t dd = r0 - c0;
-      const bool dchunk = m.seg.self_pairs && dd > -R && dd < 64;
-      uint64_t mk[R];
+    wave_sync();
 #pragma unroll
-      for (int j = 0; j < R; ++j) {
-        uint32_t bits = gap_bits(rb[j].x1, cbx.x0) | gap_bits(cbx.x1, rb[j].x0) |
-                        gap_bits(rb[j].y1, cbx.y0) | gap_bits(cbx.y1, rb[j].y0);
-        if (Z3) bits |= gap_bits(rb[j].hi, cbx.lo) | gap_bits(cbx.hi, rb[j].lo);
-        // rows and columns past the block never survive, whatever the
-        // infinities of the other side's bounds make of the test
-        mk[j] = j < nr ? __ballot(valid && (int32_t)bits >= 0) : 0ull;
+    for (int a = 0; a < D; ++a) {
+      const uint64_t v = s.bm[a][w][lane];
+      s.bm[a][w][lane] = (uint64_t)half_prefix_or((uint32_t)(v >> 32)) << 32 |
+                         half_prefix_or((uint32_t)v);
+    }
+  }
+  __syncthreads();
+
+  const int64_t row = r0 + wave * 64 + lane;  // in the segment
+  if (r0 + wave * 64 >= g.na) return;         // uniform in the wavefront
+  Bounds rb = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (row < g.na) rb = box_bounds<K, FIXED, Z3>(m.a, g.a0 + row);
+  const bool live = row < g.na && !(Z3 && !(rb.hi > rb.lo));
+  if (Z3) rb.hi = below(rb.hi);
+  // bit-set entries: columns that begin at or below the row's end, and end
+  // at or above its start
+  int e0[D], e1[D];
+  {
+    const float l[3] = {rb.x0, rb.y0, rb.lo}, h[3] = {rb.x1, rb.y1, rb.hi};
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      e0[a] = bin_of(h[a], lo[a], scale[a]);
+      e1[a] = 2 * kBins - 1 - bin_of(l[a], lo[a], scale[a]);
+    }
+  }
+  const int64_t tr = row >> RL;
+  const int64_t u = tile0 + tr * col_tiles_of(g, RL) + tc;
+  const bool have = row < (tile_rows_of(g, RL) << RL) && u < m.tile_capacity;
+  uint64_t* state = m.tile_mask + u * kMaskWords + (lane & (R - 1));
+  uint32_t n = 0u;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    uint64_t keep = 0ull;
+    if (w * 64 < nc) {  // uniform
+      uint64_t cand = live ? ~0ull : 0ull;
+#pragma unroll
+      for (int a = 0; a < D; ++a) cand &= s.bm[a][w][e0[a]] & s.bm[a][w][e1[a]];
+      if (m.seg.self_pairs) {  // the diagonal
+        const int64_t dd = row - (cb + w * 64);
+        if (dd >= 0 && dd < 64) cand &= ~(1ull << dd);
       }
-      if (dchunk) {  // rare: the chunk holds part of the diagonal
-        const int d = (int)dd;
-#pragma unroll
-        for (int j = 0; j < R; ++j)
-          if (d + j >= 0 && d + j < 64) mk[j] &= ~(1ull << (d + j));
-      }
-      // word ci * R + j of the tile goes to that lane
-      static_for<R>([&](auto jc) {
-        constexpr int j = decltype(jc)::value;
-        mlo = write_lane<ci * R + j>(mlo, (uint32_t)mk[j]);
-        mhi = write_lane<ci * R + j>(mhi, (uint32_t)(mk[j] >> 32));
-        n += (uint32_t)__popcll(mk[j]);
-      });
-    });
-    // the tile's output rows, each one contiguous run of up to 256 values (0,
-    // or 1 where a self block's diagonal crosses); the exact kernel later
-    // overwrites the survivors
-    const int64_t dg = m.seg.self_pairs ? r0 - cb : INT64_MIN / 2;  // diagonal column of row 0
-    for (int j = 0; j < nr; ++j) {
-      float* row = out_rows + (int64_t)j * g.nb + cb;
-      const bool drow = dg + j >= 0 && dg + j < C;  // uniform
-#pragma unroll
-      for (int ci = 0; ci < C / 64; ++ci) {
-        const int col = ci * 64 + lane;
-        if (cb + col < ce) row[col] = (drow && col == dg + j) ? 1.f : 0.f;
+      while (cand != 0ull) {
+        const int j = w * 64 + __builtin_ctzll(cand);
+        const uint64_t rest = cand & (cand - 1ull);
+        const float4 b = s.xy[j];
+        uint32_t bits = gap_bits(rb.x1, b.x) | gap_bits(b.z, rb.x0) | gap_bits(rb.y1, b.y) |
+                        gap_bits(b.w, rb.y0);
+        if constexpr (Z3) {
+          const float2 z = s.z[j];
+          bits |= gap_bits(rb.hi, z.x) | gap_bits(z.y, rb.lo);
+        }
+        if ((int32_t)bits >= 0) keep |= cand ^ rest;
+        cand = rest;
       }
     }
-    if (u < m.tile_capacity) {
-      // the tile's state for the fill pass: bits, origin, row length
-      uint64_t mword = ((uint64_t)mhi << 32) | mlo;
-      if (lane == kBitWords) mword = (uint64_t)(g.out0 + r0 * g.nb + cb);
-      if (lane == kBitWords + 1) mword = (uint64_t)g.nb;
-      if (lane < kMaskWords) m.tile_mask[u * kMaskWords + lane] = mword;
-      if (lane == 0) m.tile_count[u] = (int32_t)n;
-    } else if (lane == 0) {
+    n += (uint32_t)__popcll(keep);
+    if (have) state[w * R] = keep;
+  }
+  // the tile's count: its R rows are R neighbouring lanes
+#pragma unroll
+  for (int d = 1; d < R; d <<= 1) n += (uint32_t)__shfl_xor((int)n, d);
+  if ((lane & (R - 1)) == 0 && row < g.na) {
+    if (have) {
+      m.tile_count[u] = (int32_t)n;
+      state[kBitWords] = (uint64_t)(g.out0 + row * g.nb + cb);
+      state[kBitWords + 1] = (uint64_t)g.nb;
+    } else {
       atomicOr(m.err, kErrCapacity);
     }
   }
 }
 
-// Fill pass: the survivors' output indices, read from the tile state the
-// count pass wrote (bits, origin, row length), go to the tile's range of the
-// work list (chunk-major, the order of the bits): lane w writes the bits of
-// word w, from the exclusive prefix of the words' counts.  A tile costs one
-// round of independent loads (prefetched), no segment lookup.
-__global__ __launch_bounds__(kCullBlock) void k_matrix_fill(CullArgs m) {
-  constexpr int WAVES = kCullBlock / 64;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+template <int K, bool FIXED, bool Z3, int R>
+__global__ __launch_bounds__(kCullBlock) void k_matrix_cull(CullArgs m) {
+  static_assert(R == 4 || R == 8 || R == 16, "tile rows");
+  constexpr int C = kTilePairs / R;
+  constexpr int RL = R == 4 ? 2 : (R == 8 ? 3 : 4);
+  __shared__ MaskLds<Z3, C> s_mask;
+  __shared__ SegScan s_scan;
   const bool segmented = m.seg.a_off != nullptr;
-  int64_t total = segmented ? m.seg.tile_prefix[m.seg.nseg] : m.single_tiles;
-  total = total < m.tile_capacity ? total : m.tile_capacity;
-  int64_t u0, u1;
-  wave_tiles(total, (int64_t)blockIdx.x * WAVES + wave, (int64_t)gridDim.x * WAVES, u0, u1);
-  // the next tile's state and start are loaded while this tile is written
-  uint64_t word_next = 0ull;
-  int64_t start_next = 0;
-  if (u0 < u1) {
-    word_next = lane < kMaskWords ? m.tile_mask[u0 * kMaskWords + lane] : 0ull;
-    start_next = m.tile_start[u0];
+  auto units_of = [&](const Segment& g) { return mask_units_of(g, RL); };
+  UnitSeg us = {load_segment(m.seg, 0), 0, 0};
+  int64_t total = m.single_units;
+  if (segmented) {
+    scan_segments(m.seg, s_scan, units_of);
+    total = s_scan.total;
+    if (blockIdx.x == 0) write_prefixes(m, s_scan);
   }
-  for (int64_t u = u0; u < u1; ++u) {
-    const uint64_t word = word_next;
-    const int64_t start = start_next;
-    if (u + 1 < u1) {
-      word_next = lane < kMaskWords ? m.tile_mask[(u + 1) * kMaskWords + lane] : 0ull;
-      start_next = m.tile_start[u + 1];
-    }
-    const uint64_t bits = lane < kBitWords ? word : 0ull;
-    if (__ballot(bits != 0ull) == 0ull) continue;  // uniform: an empty tile
-    // (the lane reads return int: each half is taken as unsigned, or a low
-    // half with its top bit set would sign-extend over the high half)
-    const int64_t origin = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(word >> 32), kBitWords) << 32) |
-                                     (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)word, kBitWords));
-    const int64_t nb = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(word >> 32), kBitWords + 1) << 32) |
-                                 (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)word, kBitWords + 1));
-    // every lane writes the survivors of its own word: its first slot is the
-    // exclusive prefix of the words' bit counts
-    const int cnt = __popcll(bits);
-    int incl = cnt;
-#pragma unroll
-    for (int d = 1; d < kBitWords; d <<= 1) {
-      const int o = __shfl_up(incl, d);
-      if (lane >= d) incl += o;
-    }
-    int64_t slot = start + (incl - cnt);
-    const int rl = m.seg.rows_log2;
-    const int j = lane & ((1 << rl) - 1), c = lane >> rl;
-    const int64_t first = origin + (int64_t)j * nb + c * 64;
-    uint64_t w = bits;
-    while (w != 0ull) {
-      const int b = __builtin_ctzll(w);
-      w &= w - 1ull;
-      if (slot < m.capacity) m.pair_id[slot] = first + b;
-      ++slot;
-    }
+  for (int64_t u = blockIdx.x; u < total; u += gridDim.x) {
+    if (segmented) us = find_unit(m.seg, s_scan, u, units_of);
+    const int64_t nct = col_tiles_of(us.g, RL);
+    int64_t rc, tc;
+    divmod(u - us.unit0, nct, rc, tc);
+    mask_unit<K, FIXED, Z3, R>(m, us.g, us.tile0, rc * kUnitRows, tc, s_mask);
   }
 }
 
-// Exclusive prefix of the tile counts in two parallel passes over chunks of
-// kScanChunk tiles: k_scan_totals sums every chunk; k_scan_apply rescans its
-// chunk in LDS, adds the totals of the chunks before it, writes tile_start,
-// clamps the counts to what the capacity holds and (last chunk) the total.
+// Sums of the tile counts over chunks of kScanChunk tiles, for tables too large
+// for every workgroup of the list pass to sum the counts before its own.
 constexpr int kScanChunk = kScanBlock * 4;
 
 __device__ __forceinline__ int64_t scan_tiles(const int64_t* tile_prefix, int nseg,
@@ -572,112 +678,200 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_totals(const int64_t* tile_
   if (threadIdx.x == kScanBlock - 1) totals[blockIdx.x] = v;
 }
 
-__global__ __launch_bounds__(kScanBlock) void k_scan_apply(const int64_t* tile_prefix, int nseg,
-                                                           int64_t single_tiles,
-                                                           int64_t tile_capacity,
-                                                           const int64_t* totals,
-                                                           int64_t* tile_start,
-                                                           int32_t* tile_count, int64_t* count,
-                                                           int64_t capacity, int* err) {
-  __shared__ int64_t s_w[kScanBlock / 64];
-  const int64_t nt = scan_tiles(tile_prefix, nseg, single_tiles, tile_capacity);
-  const int64_t nchunks = (nt + kScanChunk - 1) / kScanChunk;
-  const int64_t c0 = (int64_t)blockIdx.x * kScanChunk;
-  if (c0 >= nt) {  // uniform; an empty matrix still publishes its total
-    if (blockIdx.x == 0 && threadIdx.x == 0) *count = 0;
+struct ListArgs {
+  SegArgs seg;
+  int64_t single_tiles;
+  float* iou;
+  int64_t list_blocks;  // workgroups of the list; the others fill the output
+  int64_t tile_capacity;
+  const int32_t* tile_count;
+  const int64_t* totals;  // sums of the chunks of kScanChunk tiles, or NULL
+  const uint64_t* tile_mask;
+  int64_t* tile_start;
+  int64_t* pair_id;
+  int64_t capacity;
+  int64_t* count;
+  int* err;
+};
+
+// ---- the work list ------------------------------------------------------
+// Sum of the counts of tiles [0, t) by a workgroup of kListBlock threads
+// (every thread gets it): whole chunks from the totals when they were taken
+// (large tables), the rest from the counts, 16 bytes a load when aligned.
+__device__ __forceinline__ int64_t sum_before(const int32_t* cnt, const int64_t* totals, int64_t t,
+                                              int64_t* s_w) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int64_t first = 0, v = 0;
+  if (totals != nullptr) {
+    const int64_t chunks = t / kScanChunk;
+    for (int64_t k = tid; k < chunks; k += kListBlock) v += totals[k];
+    first = chunks * kScanChunk;
+  }
+  if ((reinterpret_cast<uintptr_t>(cnt) & 15) == 0) {  // uniform (chunks are multiples of 4)
+    const int64_t n4 = (t - first) >> 2;
+    const int4* c4 = reinterpret_cast<const int4*>(cnt + first);
+    int64_t k = tid;
+    for (; k + 3 * kListBlock < n4; k += 4 * kListBlock) {  // four loads in flight
+      const int4 a = c4[k], b = c4[k + kListBlock], c = c4[k + 2 * kListBlock],
+                 d = c4[k + 3 * kListBlock];
+      v += (int64_t)(a.x + a.y + a.z + a.w) + (b.x + b.y + b.z + b.w) + (c.x + c.y + c.z + c.w) +
+           (d.x + d.y + d.z + d.w);
+    }
+    for (; k < n4; k += kListBlock) {
+      const int4 a = c4[k];
+      v += a.x + a.y + a.z + a.w;
+    }
+    first += n4 << 2;
+  }
+  for (int64_t k = first + tid; k < t; k += kListBlock) v += cnt[k];
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) v += __shfl_xor(v, d);
+  if (lane == 0) s_w[wave] = v;
+  __syncthreads();
+  v = 0;
+#pragma unroll
+  for (int w = 0; w < kListBlock / 64; ++w) v += s_w[w];
+  __syncthreads();
+  return v;
+}
+
+// A wavefront's step of the fill: zeros to values [o, o + 256) of the `size`
+// ones at out (o may be below 0, and the last step past the end), four a lane,
+// o chosen so that each lane's four are one aligned store.
+__device__ __forceinline__ void fill_step(float* out, int64_t size, int64_t o) {
+  const int64_t e = o + 4 * (threadIdx.x & 63);
+  if (e >= 0 && e + 4 <= size) {
+    *reinterpret_cast<float4*>(out + e) = make_float4(0.f, 0.f, 0.f, 0.f);
+  } else {  // the first or last values
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (e + c >= 0 && e + c < size) out[e + c] = 0.f;
+  }
+}
+
+// The output's zeros (the exact kernel, later, writes the survivors and the
+// self diagonals over them), by the list pass's other workgroups: the list is
+// bound by latency and the fill by memory, so they share the chip.  Where the
+// blocks cover the output without gaps it is one flat stream, a step a
+// workgroup: one aligned 16-byte store a lane and short-lived wavefronts
+// write 6.7 TB/s here (348 MB in 52 us; grid-stride loops 5.6, and the rows
+// of the masks' tiles, as the masks were made, 3.9, each row ending in two
+// partial cache lines).  Otherwise each block is filled by itself, found from
+// a scan of the segments, and gaps are left alone.
+__device__ __forceinline__ void fill_output(const ListArgs& m, int64_t b, int64_t nblk,
+                                            SegScan& sc) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const SegArgs& a = m.seg;
+  int64_t size = a.a_count * a.b_count;
+  if (a.a_off != nullptr) size = a.nseg < kMaxSeg ? m.seg.tile_prefix[a.nseg + 1] : -1;
+  if (size >= 0) {
+    const int mis = (int)((reinterpret_cast<uintptr_t>(m.iou) >> 2) & 3);
+    for (int64_t o = b * kFillStep + wave * 256 - mis; o < size; o += nblk * kFillStep)
+      fill_step(m.iou, size, o);
     return;
   }
-  // base: totals of the chunks before this one
-  int64_t b = 0;
-  for (int64_t k = threadIdx.x; k < blockIdx.x; k += kScanBlock) b += totals[k];
-  b = block_inclusive_scan(b, s_w);
-  __shared__ int64_t s_base;
-  if (threadIdx.x == kScanBlock - 1) s_base = b;
-  __syncthreads();
-  int64_t run = s_base;
-  // this chunk: kScanChunk / kScanBlock consecutive tiles per thread
-  constexpr int PER = kScanChunk / kScanBlock;
-  int64_t c[PER];
-  int64_t v = 0;
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int64_t t = c0 + (int64_t)threadIdx.x * PER + k;
-    c[k] = t < nt ? tile_count[t] : 0;
-    v += c[k];
-  }
-  const int64_t incl = block_inclusive_scan(v, s_w);
-  run += incl - v;
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int64_t t = c0 + (int64_t)threadIdx.x * PER + k;
-    if (t < nt) {
-      tile_start[t] = run;
-      int64_t room = capacity - run;
-      room = room < 0 ? 0 : (room > c[k] ? c[k] : room);
-      tile_count[t] = (int32_t)room;
-    }
-    run += c[k];
-  }
-  if (blockIdx.x == nchunks - 1 && threadIdx.x == kScanBlock - 1) {
-    *count = run;
-    if (run > capacity) atomicOr(err, kErrCapacity);
+  nblk = min(nblk, (int64_t)kFillSegBlocks);
+  if (b >= nblk) return;  // uniform
+  auto units_of = [&](const Segment& g) { return fill_units_of(g, m.iou); };
+  scan_segments(a, sc, units_of);
+  for (int64_t u = b; u < sc.total; u += nblk) {
+    const UnitSeg us = find_unit(a, sc, u, units_of);
+    float* out = m.iou + us.g.out0;
+    const int mis = (int)((reinterpret_cast<uintptr_t>(out) >> 2) & 3);
+    fill_step(out, us.g.na * us.g.nb, (u - us.unit0) * kFillStep + wave * 256 - mis);
   }
 }
 
-// The same exclusive prefix in one workgroup, for tile tables of at most
-// kScanSmall entries (a call's tile capacity bounds its tile count): one
-// coalesced round of loads into LDS (a tile holds at most 2048 survivors, so
-// its count fits 16 bits and a prefix over 8192 tiles 32 bits), the scan of
-// each thread's run of 8 tiles, and one coalesced round of stores: one
-// launch in place of the two passes.
-constexpr int64_t kScanSmall = 8 * kScanBlock;
-
-__global__ __launch_bounds__(kScanBlock) void k_scan_small(const int64_t* tile_prefix, int nseg,
-                                                           int64_t single_tiles,
-                                                           int64_t tile_capacity,
-                                                           int64_t* tile_start,
-                                                           int32_t* tile_count, int64_t* count,
-                                                           int64_t capacity, int* err) {
-  constexpr int PER = kScanSmall / kScanBlock;
-  __shared__ uint16_t s_cnt[kScanSmall];
-  __shared__ int32_t s_pre[kScanSmall];
-  __shared__ int64_t s_w[kScanBlock / 64];
-  const int t = threadIdx.x;
-  const int64_t nt = scan_tiles(tile_prefix, nseg, single_tiles, tile_capacity);
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int i = k * kScanBlock + t;
-    s_cnt[i] = i < nt ? (uint16_t)tile_count[i] : (uint16_t)0;
+// Lays out the work list: the exclusive prefix of the tile counts, and the
+// survivors' output indices from the tile state the count pass wrote (bits,
+// origin, row length), each tile's in the order of its bits (chunk-major).  A
+// workgroup takes a contiguous range of tiles, whose start it sums from the
+// counts before it, and walks it kListTiles tiles at a time: a scan of their
+// counts, then two tiles a wavefront step, a lane for each word of bits.
+// One launch in place of two or three (the scan's and this one's own): bound
+// by latency, and the sums are L2 reads (c5: 45.7 k counts, 183 KB).
+__global__ __launch_bounds__(kListBlock) void k_matrix_list(ListArgs m) {
+  __shared__ SegScan s_scan;
+  constexpr int WAVES = kListBlock / 64;
+  __shared__ int64_t s_w[WAVES];
+  __shared__ int64_t s_start[kListTiles];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if ((int64_t)blockIdx.x >= m.list_blocks) {
+    fill_output(m, (int64_t)blockIdx.x - m.list_blocks, (int64_t)gridDim.x - m.list_blocks, s_scan);
+    return;
   }
-  __syncthreads();
-  int64_t v = 0;
-#pragma unroll
-  for (int k = 0; k < PER; ++k) v += s_cnt[t * PER + k];
-  const int64_t incl = block_inclusive_scan(v, s_w);
-  int32_t run = (int32_t)(incl - v);
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    s_pre[t * PER + k] = run;
-    run += s_cnt[t * PER + k];
+  int64_t nt = m.seg.a_off != nullptr ? m.seg.tile_prefix[m.seg.nseg] : m.single_tiles;
+  nt = nt < m.tile_capacity ? nt : m.tile_capacity;
+  const int64_t per = (nt + m.list_blocks - 1) / m.list_blocks;
+  const int64_t t0 = blockIdx.x * per, t1 = min(nt, t0 + per);
+  if (t0 >= t1) {  // uniform; an empty matrix still publishes its total
+    if (blockIdx.x == 0 && tid == 0) *m.count = 0;
+    return;
   }
-  __syncthreads();
+  int64_t run = sum_before(m.tile_count, m.totals, t0, s_w);
+  for (int64_t b0 = t0; b0 < t1; b0 += kListTiles) {
+    const int nb_tiles = (int)min((int64_t)kListTiles, t1 - b0);
+    // one tile a thread: wave scan, then the waves before it
+    const int c = tid < nb_tiles ? m.tile_count[b0 + tid] : 0;
+    int incl = c;  // at most kListTiles * 2048
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int i = k * kScanBlock + t;
-    if (i < nt) {
-      const int64_t start = s_pre[i], c = s_cnt[i];
-      tile_start[i] = start;
-      int64_t room = capacity - start;
-      room = room < 0 ? 0 : (room > c ? c : room);
-      tile_count[i] = (int32_t)room;
+    for (int d = 1; d < 64; d <<= 1) {
+      const int o = __shfl_up(incl, d);
+      if (lane >= d) incl += o;
     }
+    if (lane == 63) s_w[wave] = incl;
+    __syncthreads();
+    int64_t start = run + incl - c;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+      if (w < wave) start += s_w[w];
+      run += s_w[w];
+    }
+    s_start[tid] = start;
+    if (tid < nb_tiles) m.tile_start[b0 + tid] = start;
+    __syncthreads();
+    const int word = lane & (kBitWords - 1);
+    const int rl = m.seg.rows_log2;
+    const int j = word & ((1 << rl) - 1), ch = word >> rl;
+    uint64_t bits_next = 0ull;
+    int64_t origin_next = 0, nb_next = 0;
+    auto load = [&](int k) {
+      const bool in = k + (lane >> 5) < nb_tiles;
+      const uint64_t* st = m.tile_mask + (b0 + k + (lane >> 5)) * kMaskWords;
+      bits_next = in ? st[word] : 0ull;
+      origin_next = in ? (int64_t)st[kBitWords] : 0;
+      nb_next = in ? (int64_t)st[kBitWords + 1] : 0;
+    };
+    load(wave * 2);
+    for (int k = wave * 2; k < nb_tiles; k += 2 * WAVES) {  // uniform
+      const uint64_t bits = bits_next;
+      const int64_t first = origin_next + (int64_t)j * nb_next + ch * 64;
+      load(k + 2 * WAVES);  // the next two tiles' state
+      // the word's first slot: the exclusive prefix of the words' bit counts
+      const int cnt = __popcll(bits);
+      int pre = cnt;
+#pragma unroll
+      for (int d = 1; d < kBitWords; d <<= 1) {
+        const int o = __shfl_up(pre, d, kBitWords);
+        if (word >= d) pre += o;
+      }
+      int64_t slot = s_start[min(k + (lane >> 5), kListTiles - 1)] + (pre - cnt);
+      uint64_t w = bits;
+      while (w != 0ull) {
+        const int b = __builtin_ctzll(w);
+        w &= w - 1ull;
+        if (slot < m.capacity) m.pair_id[slot] = first + b;
+        ++slot;
+      }
+    }
+    __syncthreads();  // s_start is the next round's
   }
-  if (t == kScanBlock - 1) {
-    *count = incl;
-    if (incl > capacity) atomicOr(err, kErrCapacity);
+  if (t1 == nt && tid == 0) {
+    *m.count = run;
+    if (run > m.capacity) atomicOr(m.err, kErrCapacity);
   }
 }
-
 struct ExactArgs {
   SegArgs seg;
   PolyArgs a, b;
@@ -690,25 +884,12 @@ struct ExactArgs {
   int cap;
   int* err;
   unsigned long long* stats;  // path statistics (NULL: off)
+  // an overflowing list's tile counts are cut to its capacity here
+  const int64_t* tile_start;
+  int32_t* tile_count;
+  int64_t tile_capacity;
+  int64_t single_tiles;
 };
-
-__device__ __forceinline__ int64_t wave_first(int64_t v) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// Quotient and remainder of a non-negative index by a positive divisor below
-// 2^24 (32-bit division when the index allows it).
-__device__ __forceinline__ void divmod(int64_t v, int64_t d, int64_t& q, int64_t& r) {
-  if (v < (int64_t)0xffffffff) {
-    const uint32_t q32 = (uint32_t)v / (uint32_t)d;
-    q = q32;
-  } else {
-    q = v / d;
-  }
-  r = v - q * d;
-}
 
 // Segment, row and column (within the segment) of a flat output index.  The
 // work list is in output order, so the entries of one wavefront mostly share
@@ -740,6 +921,22 @@ __device__ __forceinline__ bool locate(const SegArgs& sa, int64_t pid, SegCache&
   return r < g.na;
 }
 
+// The 1s on the diagonals of self blocks, a row a thread, by the last
+// workgroups of the exact pass (the ones that most often have no entries).
+__device__ __forceinline__ void write_diagonals(const SegArgs& a, float* iou) {
+  const int64_t threads = (int64_t)gridDim.x * kExactBlock;
+  for (int64_t r0 = ((int64_t)gridDim.x - 1 - blockIdx.x) * kExactBlock + (threadIdx.x & ~63);
+       r0 < a.a_count; r0 += threads) {  // the wavefront's 64 rows
+    const int64_t row = r0 + (threadIdx.x & 63);
+    const bool segmented = a.a_off != nullptr;
+    const int s0 = segmented ? wave_find_segment(a.a_off, a.nseg, wave_first(r0)) : 0;
+    Segment g = load_segment(a, s0);
+    if (segmented && row >= g.a0 + g.na) g = load_segment(a, find_segment(a.a_off, a.nseg, row));
+    const int64_t r = row - g.a0;
+    if (g.ok && r >= 0 && r < g.na) iou[g.out0 + r * (g.nb + 1)] = 1.f;
+  }
+}
+
 template <int K, bool FIXED, bool Z3>
 __global__ __launch_bounds__(kExactBlock)
 __attribute__((amdgpu_waves_per_eu(4))) void k_matrix_exact(ExactArgs m) {
@@ -748,7 +945,17 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_matrix_exact(ExactArgs m) {
   __shared__ uint16_t s_cd[CAP * kExactBlock];
   const int tid = threadIdx.x;
   int64_t n = *m.count;
-  n = n < m.capacity ? n : m.capacity;
+  if (n > m.capacity) {  // uniform; an overflow
+    n = m.capacity;
+    int64_t nt = m.seg.tile_prefix != nullptr ? m.seg.tile_prefix[m.seg.nseg] : m.single_tiles;
+    nt = nt < m.tile_capacity ? nt : m.tile_capacity;
+    for (int64_t t = (int64_t)blockIdx.x * kExactBlock + tid; t < nt;
+         t += (int64_t)gridDim.x * kExactBlock) {
+      const int64_t room = max((int64_t)0, m.capacity - m.tile_start[t]);
+      if (room < m.tile_count[t]) m.tile_count[t] = (int32_t)room;
+    }
+  }
+  if (m.seg.self_pairs) write_diagonals(m.seg, m.iou);
   // each wavefront a contiguous range of entries, 64 at a time: consecutive
   // entries mostly share a segment, which is then searched once
   const int64_t wid = ((int64_t)blockIdx.x * kExactBlock + tid) >> 6;
@@ -1169,15 +1376,12 @@ int matrix_forward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_t
   const int K = reg_k(a.kmax, b.kmax);
   const bool segmented = a_off != nullptr;
   int64_t single_tiles = 0;
+  int64_t* pre = nullptr;
   if (segmented) {
     // in the caller's saved state when it has room, for the backward
-    int64_t* pre = saved->seg_prefix != nullptr ? saved->seg_prefix : ctx.prefix;
+    pre = saved->seg_prefix != nullptr ? saved->seg_prefix : ctx.prefix;
     sa.tile_prefix = pre;
     sa.group_prefix = pre + (kMaxSeg + 1);
-    prof_begin(ctx.prof, stream);
-    hipLaunchKernelGGL(k_seg_prep, dim3(1), dim3(256), 0, stream, sa, ctx.err, pre,
-                       pre + (kMaxSeg + 1));
-    prof_end(ctx.prof, "k_seg_prep", stream);
   } else {
     if (a.count == 0 || b.count == 0) return hipGetLastError() == hipSuccess ? DGAL_OK : DGAL_EHIP;
     single_tiles = ceil_div(a.count, R) * ceil_div(b.count, kTilePairs / R);
@@ -1186,15 +1390,35 @@ int matrix_forward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_t
   c.seg = sa;
   c.a = poly_args(a, K);
   c.b = poly_args(b, K);
-  c.single_tiles = single_tiles;
-  c.iou = iou;
-  c.pair_id = saved->pair_id;
-  c.capacity = saved->capacity;
-  c.tile_start = saved->tile_start;
   c.tile_count = saved->tile_count;
   c.tile_capacity = saved->tile_capacity;
   c.tile_mask = saved->tile_mask;
+  c.tile_prefix = pre;
+  c.group_prefix = segmented ? pre + (kMaxSeg + 1) : nullptr;
   c.err = ctx.err;
+  // the units' workgroups; with segments, whose sizes are on the device, they
+  // walk the units in grid strides
+  int64_t cull_grid = (int64_t)ctx.cus * (shape.cull_mult > 0 ? shape.cull_mult : 32) / 4;
+  if (segmented) {
+    c.single_units = 0;
+    cull_grid = std::max<int64_t>(1, std::min(cull_grid, saved->tile_capacity));
+  } else {
+    c.single_units = ceil_div(a.count, kUnitRows) * ceil_div(b.count, kTilePairs / R);
+    cull_grid = std::min(cull_grid, c.single_units);
+  }
+  ListArgs li;
+  li.seg = sa;
+  li.single_tiles = single_tiles;
+  li.iou = iou;
+  li.tile_capacity = saved->tile_capacity;
+  li.tile_count = saved->tile_count;
+  li.totals = nullptr;
+  li.tile_mask = saved->tile_mask;
+  li.tile_start = saved->tile_start;
+  li.pair_id = saved->pair_id;
+  li.capacity = saved->capacity;
+  li.count = saved->count;
+  li.err = ctx.err;
   ExactArgs x;
   x.seg = sa;
   x.a = c.a;
@@ -1208,10 +1432,10 @@ int matrix_forward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_t
   x.cap = a.kmax + b.kmax;
   x.err = ctx.err;
   x.stats = ctx.stats;
-  // 32 workgroups per CU by default: ranges of one or two tiles a wavefront
-  // (c5: 110 us at 32, 48 or 64, 116 us at 16); a single block is capped below
-  int64_t cull_grid = (int64_t)ctx.cus * (shape.cull_mult > 0 ? shape.cull_mult : 32);
-  if (!segmented) cull_grid = std::min(cull_grid, ceil_div(single_tiles, kCullBlock / 64));
+  x.tile_start = saved->tile_start;
+  x.tile_count = saved->tile_count;
+  x.tile_capacity = saved->tile_capacity;
+  x.single_tiles = single_tiles;
   const int exact_grid = ctx.cus * (shape.exact_mult > 0 ? shape.exact_mult : 8);
   const bool fixed = a.nv == nullptr && b.nv == nullptr && a.kmax == K && b.kmax == K &&
                      aligned(a.xy, 16) && aligned(b.xy, 16);
@@ -1224,31 +1448,25 @@ int matrix_forward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_t
     else if (R == 16) hipLaunchKernelGGL((k_matrix_cull<KK, FX, ZZ, 16>), cg, cb, 0, stream, c);
     else hipLaunchKernelGGL((k_matrix_cull<KK, FX, ZZ, 8>), cg, cb, 0, stream, c);
     prof_end(ctx.prof, "k_matrix_cull", stream);
-    if (saved->tile_capacity <= kScanSmall) {  // few tiles: one launch
-      prof_begin(ctx.prof, stream);
-      hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(kScanBlock), 0, stream, sa.tile_prefix,
-                         sa.nseg, single_tiles, saved->tile_capacity, saved->tile_start,
-                         saved->tile_count, saved->count, saved->capacity, ctx.err);
-      prof_end(ctx.prof, "k_scan_small", stream);
-    } else {
-      const int64_t chunks = std::max<int64_t>(1, ceil_div(saved->tile_capacity, kScanChunk));
+    if (saved->tile_capacity > kListDirect) {
+      const int64_t chunks = ceil_div(saved->tile_capacity, kScanChunk);
       prof_begin(ctx.prof, stream);
       hipLaunchKernelGGL(k_scan_totals, dim3((unsigned)chunks), dim3(kScanBlock), 0, stream,
                          sa.tile_prefix, sa.nseg, single_tiles, saved->tile_capacity,
                          saved->tile_count, ctx.scan);
       prof_end(ctx.prof, "k_scan_totals", stream);
-      prof_begin(ctx.prof, stream);
-      hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)chunks), dim3(kScanBlock), 0, stream,
-                         sa.tile_prefix, sa.nseg, single_tiles, saved->tile_capacity, ctx.scan,
-                         saved->tile_start, saved->tile_count, saved->count, saved->capacity,
-                         ctx.err);
-      prof_end(ctx.prof, "k_scan_apply", stream);
+      li.totals = ctx.scan;
     }
-    // the fill walks ~8 resident waves per SIMD, each over a contiguous range of tiles
+    // the list's workgroups first, then the fill's, a step each up to the
+    // launch's limit on threads
+    li.list_blocks = std::max<int64_t>(
+        1, std::min<int64_t>((int64_t)ctx.cus * 2, ceil_div(saved->tile_capacity, 16)));
+    const int64_t fill = ceil_div((segmented ? out_size : a.count * b.count) + 3, kFillStep);
     prof_begin(ctx.prof, stream);
-    hipLaunchKernelGGL(k_matrix_fill, dim3((unsigned)std::max<int64_t>(1, (int64_t)ctx.cus * 8)),
-                       dim3(kCullBlock), 0, stream, c);
-    prof_end(ctx.prof, "k_matrix_fill", stream);
+    hipLaunchKernelGGL(k_matrix_list,
+                       dim3((unsigned)(li.list_blocks + std::min<int64_t>(1 << 23, fill))),
+                       dim3(kListBlock), 0, stream, li);
+    prof_end(ctx.prof, "k_matrix_list", stream);
     prof_begin(ctx.prof, stream);
     hipLaunchKernelGGL((k_matrix_exact<KK, FX, ZZ>), dim3(exact_grid), dim3(kExactBlock), 0,
                        stream, x);
