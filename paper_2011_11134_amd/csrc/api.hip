@@ -687,6 +687,9 @@ int dgal_iou_simple_backward(dgal_ctx* ctx, dgal_polys a, dgal_polys b, const fl
   args.xmask = xmask;
   args.smask = smask;
   args.inside = inside;
+  // the gradient rows are written with the same vector width as the inputs
+  args.a.vec4 = args.a.vec4 && aligned(grad_a_xy, 16);
+  args.b.vec4 = args.b.vec4 && aligned(grad_b_xy, 16);
   args.ga_xy = grad_a_xy;
   args.gb_xy = grad_b_xy;
   const hipError_t e_ = [&] {

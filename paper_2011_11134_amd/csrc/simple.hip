@@ -35,12 +35,22 @@ constexpr int simple_block() {
   return K == 8 ? 128 : 256;
 }
 
-// At K = 8 both kernels are held to 3 waves per SIMD (at most 168 VGPRs):
-// left alone the backward takes more and runs 2; held to 4 it spills
-// 36 bytes a lane to scratch (HBM traffic) and measured slower.
+// At K = 8 both kernels run 4 waves per SIMD: 128 (forward) and 160 (backward)
+// bytes of LDS a lane against 160 KiB a CU, and at most 128 VGPRs, so that
+// 262,144 pairs (4,096 wavefronts) are one round.  Three waves per SIMD (192
+// bytes; 168 VGPRs and 40 bytes a lane of spills in the backward) took two
+// rounds (forward 32 us, backward 46 us there, now 28.5 and 23).
 template <int K>
 constexpr int simple_waves() {
-  return K == 8 ? 3 : 1;
+  return K == 8 ? 4 : 1;
+}
+
+// Values the compiler cannot trace to their first computation, so that what
+// follows is computed again from them instead of being kept in registers.
+template <int K>
+__device__ __forceinline__ void forget(Poly<K>& P) {
+#pragma unroll
+  for (int k = 0; k < K; ++k) asm volatile("" : "+v"(P.x[k]), "+v"(P.y[k]));
 }
 
 // Row masks of the tie-ruled sign table: bit j of spr[i] when P_i is strictly
@@ -149,30 +159,51 @@ __device__ __forceinline__ uint32_t parity8(uint32_t v) { return __builtin_popco
 // Each edge of P walks the set bits of its crossing row (a wavefront takes
 // as many steps as its busiest lane's row has crossings); the crossed edge of
 // Q is read from this lane's LDS column (s_q: Q's vertices).
+//
+// Column of Q's sums: (B', M) an edge, and with GRAD (B', V1) and V2.
+template <int K, bool GRAD, int BLOCK>
+struct SimpleLds {
+  float2 q[K * BLOCK];
+  float2 bm[K * BLOCK];
+  float v2[GRAD ? K * BLOCK : 1];
+};
+
+// Q's vertices back from the lane's column (no register holds them across the
+// walk of the crossings).
+template <int K, bool GRAD, int BLOCK>
+__device__ __forceinline__ void reload_q(const SimpleLds<K, GRAD, BLOCK>& s, Poly<K>& Q) {
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const float2 v = s.q[k * BLOCK + threadIdx.x];
+    Q.x[k] = v.x;
+    Q.y[k] = v.y;
+  }
+}
+
 template <int K, bool GRAD, int BLOCK>
 __device__ __forceinline__ void crossing_sums(const Poly<K>& P, int n1, const Poly<K>& Q, int n2,
-                                              const float (&epx)[K], const float (&epy)[K],
-                                              const uint32_t (&xrow)[K], const uint32_t (&erow)[K],
-                                              bool exact, float2* __restrict__ s_q,
-                                              float4* __restrict__ s_acc, float (&B)[K],
-                                              float (&L)[K], float (&W1)[K], float (&W2)[K],
-                                              float (&Bq)[K], float (&M)[K], float (&V1)[K],
-                                              float (&V2)[K]) {
+                                              uint64_t xm, uint64_t sm, bool exact,
+                                              SimpleLds<K, GRAD, BLOCK>& s, float (&B)[K],
+                                              float (&L)[K], float (&W2)[K]) {
+  float2* s_q = s.q + threadIdx.x;
+  float2* s_bm = s.bm + threadIdx.x;
+  float* s_v2 = s.v2 + (GRAD ? threadIdx.x : 0);
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     s_q[k * BLOCK] = make_float2(Q.x[k], Q.y[k]);
-    s_acc[k * BLOCK] = make_float4(0.f, 0.f, 0.f, 0.f);
+    s_bm[k * BLOCK] = make_float2(0.f, 0.f);
+    if (GRAD) s_v2[k * BLOCK] = 0.f;
     B[k] = 0.f;
-    L[k] = 0.f;
-    W1[k] = 0.f;
+    L[k] = 0.f;  // with GRAD: W1
     W2[k] = 0.f;
   }
-  // Q's sums: .x base, .y fraction terms, .z / .w the integrals' terms
 #pragma unroll
   for (int i = 0; i < K; ++i) {
-    const int inx = next_idx<K, false>(i, n1);
-    uint32_t row = xrow[i];
-    const uint32_t er = erow[i];
+    const float pnx = next_of<K, false>(P.x, i, n1), pny = next_of<K, false>(P.y, i, n1);
+    const float ex = pnx - P.x[i], ey = pny - P.y[i];
+    uint32_t row = (uint32_t)(xm >> (8 * i)) & 0xffu;
+    const uint32_t er = (uint32_t)(sm >> (8 * i)) & 0xffu;
     while (row) {
       const uint32_t j = (uint32_t)__builtin_ctz(row);
       row &= row - 1u;
@@ -183,10 +214,10 @@ __device__ __forceinline__ void crossing_sums(const Poly<K>& P, int n1, const Po
       float o0, o1;
       if (!exact) {
         o0 = fx * (P.y[i] - q.y) - fy * (P.x[i] - q.x);
-        o1 = fx * (P.y[inx] - q.y) - fy * (P.x[inx] - q.x);
+        o1 = fx * (pny - q.y) - fy * (pnx - q.x);
       } else {
         o0 = (float)orient64(q.x, q.y, qn.x, qn.y, P.x[i], P.y[i]);
-        o1 = (float)orient64(q.x, q.y, qn.x, qn.y, P.x[inx], P.y[inx]);
+        o1 = (float)orient64(q.x, q.y, qn.x, qn.y, pnx, pny);
       }
       // The crossing point X = P_i + t e_i; its parameter on Q's edge is X's
       // projection onto that edge, not a second independent quotient: where
@@ -199,39 +230,30 @@ __device__ __forceinline__ void crossing_sums(const Poly<K>& P, int n1, const Po
       const float idn = fast_rcp(o0 - o1);
       const float t = fminf(fmaxf(o0 * idn, 0.f), 1.f);
       const float ut = fminf(fmaxf(-o1 * idn, 0.f), 1.f);
-      const float rx = fmaf(t, epx[i], P.x[i] - q.x), ry = fmaf(t, epy[i], P.y[i] - q.y);
-      const float vx = fmaf(-t, epx[i], qn.x - P.x[i]), vy = fmaf(-t, epy[i], qn.y - P.y[i]);
+      const float rx = fmaf(t, ex, P.x[i] - q.x), ry = fmaf(t, ey, P.y[i] - q.y);
+      const float vx = fmaf(-t, ex, qn.x - P.x[i]), vy = fmaf(-t, ey, qn.y - P.y[i]);
       const float ifn = fast_rcp(fmaf(fx, fx, fy * fy));
       const float sq = fminf(fmaxf((rx * fx + ry * fy) * ifn, 0.f), 1.f);
       const float us = fminf(fmaxf((vx * fx + vy * fy) * ifn, 0.f), 1.f);
       const float sg = ((er >> j) & 1u) ? 1.f : -1.f;
       const bool near_p = t < 0.5f;  // anchored at the edge's start
       B[i] += near_p ? sg : 0.f;
-      float4 a = s_acc[j * BLOCK];
+      float2 a = s_bm[j * BLOCK];
       const bool near_q = sq < 0.5f;
       a.x += near_q ? -sg : 0.f;
       if (GRAD) {
         // the fraction's term is the sum of the integrals' terms (int (1 - t)
         // + int t over the inside part is its length): not kept apart
-        W1[i] = fmaf(0.5f * sg, near_p ? -t * (2.f - t) : ut * ut, W1[i]);
+        L[i] = fmaf(0.5f * sg, near_p ? -t * (2.f - t) : ut * ut, L[i]);
         W2[i] = fmaf(0.5f * sg, near_p ? -t * t : ut * (1.f + t), W2[i]);
-        a.z = fmaf(-0.5f * sg, near_q ? -sq * (2.f - sq) : us * us, a.z);
-        a.w = fmaf(-0.5f * sg, near_q ? -sq * sq : us * (1.f + sq), a.w);
+        a.y = fmaf(-0.5f * sg, near_q ? -sq * (2.f - sq) : us * us, a.y);
+        s_v2[j * BLOCK] = fmaf(-0.5f * sg, near_q ? -sq * sq : us * (1.f + sq), s_v2[j * BLOCK]);
       } else {
         L[i] = fmaf(sg, near_p ? -t : ut, L[i]);
         a.y = fmaf(-sg, near_q ? -sq : us, a.y);
       }
-      s_acc[j * BLOCK] = a;
+      s_bm[j * BLOCK] = a;
     }
-  }
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const float4 a = s_acc[k * BLOCK];
-    Bq[k] = a.x;
-    V1[k] = a.z;
-    V2[k] = a.w;
-    M[k] = GRAD ? a.z + a.w : a.y;
-    if (GRAD) L[k] = W1[k] + W2[k];
   }
 }
 
@@ -253,38 +275,76 @@ __device__ __forceinline__ float edges(const Poly<K>& P, int n1, const Poly<K>& 
   return E;
 }
 
-// Inclusion of every vertex: P_i+1 differs from P_i by the parity of the
-// crossings on edge i; Q_j+1 from Q_j by that of column j.
+// Inclusion of every vertex, bit k of a mask: P_i+1 differs from P_i by the
+// parity of the crossings on edge i; Q_j+1 from Q_j by that of column j.
 template <int K>
-__device__ __forceinline__ void vertex_inclusion(uint32_t inside, const uint32_t (&xrow)[K],
-                                                 float (&ep)[K], float (&eq)[K]) {
+__device__ __forceinline__ void vertex_inclusion(uint32_t inside, uint64_t xm, uint32_t& ep,
+                                                 uint32_t& eq) {
+  uint64_t c = xm ^ (xm >> 32);  // column parities
+  c ^= c >> 16;
+  c ^= c >> 8;
+  const uint32_t col = (uint32_t)c & 0xffu;
   uint32_t a = inside & 1u, b = (inside >> 1) & 1u;
+  ep = 0u;
+  eq = 0u;
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    ep[k] = a ? 1.f : 0.f;
-    eq[k] = b ? 1.f : 0.f;
-    a ^= parity8(xrow[k]);
-    uint32_t col = 0u;
-#pragma unroll
-    for (int i = 0; i < K; ++i) col ^= (xrow[i] >> k) & 1u;
-    b ^= col;
+    ep |= a << k;
+    eq |= b << k;
+    a ^= parity8((uint32_t)(xm >> (8 * k)));
+    b ^= (col >> k) & 1u;
   }
 }
 
-// Cross products of consecutive vertices in the frame centred on P_0 (twice
-// the signed area of each edge's triangle with P_0), zero on padded edges.
+// Cross product of vertices k and k + 1 of V in the frame centred on (ox, oy)
+// (twice the signed area of the edge's triangle with it), zero on padded edges.
 template <int K>
-__device__ __forceinline__ void edge_cross(const Poly<K>& P, int n1, const Poly<K>& Q, int n2,
-                                           float (&cp)[K], float (&cq)[K]) {
-  const float ox = P.x[0], oy = P.y[0];
+__device__ __forceinline__ float edge_cross(const Poly<K>& V, int k, int n, float ox, float oy) {
+  const float ax = V.x[k] - ox, ay = V.y[k] - oy;
+  const float bx = next_of<K, false>(V.x, k, n) - ox, by = next_of<K, false>(V.y, k, n) - oy;
+  return k < n ? ax * by - ay * bx : 0.f;
+}
+
+// The gradient of one polygon's vertices: each vertex moves its two edges'
+// outward normals (dy, -dx) weighted by W1 of the edge that leaves it and W2 of
+// the one that arrives, and the polygon's area by its neighbours.
+template <int K>
+__device__ __forceinline__ void store_grad(const Poly<K>& V, int n, const float (&W1)[K],
+                                           const float (&W2)[K], float cI, float cA, float* out,
+                                           int kmax, bool vec4) {
+  // the last edge, which arrives at vertex 0
+  float wl = W2[2], lx = V.x[2], ly = V.y[2];
+#pragma unroll
+  for (int t = 3; t < K; ++t) {
+    wl = t == n - 1 ? W2[t] : wl;
+    lx = t == n - 1 ? V.x[t] : lx;
+    ly = t == n - 1 ? V.y[t] : ly;
+  }
+  float w2p = wl, ppx = lx, ppy = ly;
+  float npx = V.y[0] - ly, npy = lx - V.x[0];
+  float2 gv[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    const float ax = P.x[k] - ox, ay = P.y[k] - oy;
-    const float bx = next_of<K, false>(P.x, k, n1) - ox, by = next_of<K, false>(P.y, k, n1) - oy;
-    cp[k] = k < n1 ? ax * by - ay * bx : 0.f;
-    const float cx = Q.x[k] - ox, cy = Q.y[k] - oy;
-    const float dx = next_of<K, false>(Q.x, k, n2) - ox, dy = next_of<K, false>(Q.y, k, n2) - oy;
-    cq[k] = k < n2 ? cx * dy - cy * dx : 0.f;
+    const float pnx = next_of<K, false>(V.x, k, n), pny = next_of<K, false>(V.y, k, n);
+    const float ex = pnx - V.x[k], ey = pny - V.y[k];
+    const float gx = cI * (ey * W1[k] + npx * w2p) + cA * 0.5f * (pny - ppy);
+    const float gy = cI * (-ex * W1[k] + npy * w2p) + cA * 0.5f * (ppx - pnx);
+    gv[k] = k < n ? make_float2(gx, gy) : make_float2(0.f, 0.f);
+    w2p = W2[k];
+    npx = ey;
+    npy = -ex;
+    ppx = V.x[k];
+    ppy = V.y[k];
+  }
+  if (vec4) {  // kmax == K, 16-byte rows
+#pragma unroll
+    for (int k = 0; k < K; k += 2)
+      *reinterpret_cast<float4*>(out + 2 * k) =
+          make_float4(gv[k].x, gv[k].y, gv[k + 1].x, gv[k + 1].y);
+  } else {
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (k < kmax) *reinterpret_cast<float2*>(out + 2 * k) = gv[k];
   }
 }
 
@@ -292,8 +352,7 @@ template <int K>
 __global__ __launch_bounds__(simple_block<K>())
 __attribute__((amdgpu_waves_per_eu(simple_waves<K>()))) void k_simple_fwd(SimpleFwdArgs args) {
   constexpr int BLOCK = simple_block<K>();
-  __shared__ float2 s_q[K * BLOCK];
-  __shared__ float4 s_acc[K * BLOCK];
+  __shared__ SimpleLds<K, false, BLOCK> s;
   const int tid = threadIdx.x;
   const int64_t n = args.a.count;
   for (int64_t p = (int64_t)blockIdx.x * BLOCK + tid; p < n; p += (int64_t)gridDim.x * BLOCK) {
@@ -302,39 +361,46 @@ __attribute__((amdgpu_waves_per_eu(simple_waves<K>()))) void k_simple_fwd(Simple
     Poly<K> P, Q;
     load_poly<K, false>(args.a.xy, p, args.a.kmax, args.a.vec4, n1, P);
     load_poly<K, false>(args.b.xy, p, args.b.kmax, args.b.vec4, n2, Q);
-    float epx[K], epy[K], eqx[K], eqy[K];
-    const float E = edges<K>(P, n1, Q, n2, epx, epy, eqx, eqy);
-    uint32_t spr[K], sqr[K];
-    const bool exact = sign_rows<K, BLOCK>(P, n1, Q, n2, epx, epy, eqx, eqy, E, s_q + tid, spr, sqr);
-    // crossings: rows i and i+1 of spr differ at j, bits j and j+1 of sqr[i] differ
-    const uint32_t jmask = (1u << n2) - 1u;
-    uint32_t xrow[K], erow[K];
     uint64_t xm = 0ull, sm = 0ull;
+    uint32_t inside;
+    bool exact;
+    {
+      float epx[K], epy[K], eqx[K], eqy[K];
+      const float E = edges<K>(P, n1, Q, n2, epx, epy, eqx, eqy);
+      uint32_t spr[K], sqr[K];
+      exact = sign_rows<K, BLOCK>(P, n1, Q, n2, epx, epy, eqx, eqy, E, s.q + tid, spr, sqr);
+      // crossings: rows i and i+1 of spr differ at j, bits j and j+1 of sqr[i] differ
+      const uint32_t jmask = (1u << n2) - 1u;
 #pragma unroll
-    for (int i = 0; i < K; ++i) {
-      const int inx = next_idx<K, false>(i, n1);
-      const uint32_t r = sqr[i];
-      const uint32_t rn = (r >> 1) | ((r & 1u) << (n2 - 1));
-      xrow[i] = i < n1 ? (spr[i] ^ spr[inx]) & (r ^ rn) & jmask : 0u;
-      erow[i] = xrow[i] & ~spr[i];  // P_i right of Q's edge j: the edge enters Q
-      xm |= (uint64_t)xrow[i] << (8 * i);
-      sm |= (uint64_t)erow[i] << (8 * i);
+      for (int i = 0; i < K; ++i) {
+        const int inx = next_idx<K, false>(i, n1);
+        const uint32_t r = sqr[i];
+        const uint32_t rn = (r >> 1) | ((r & 1u) << (n2 - 1));
+        const uint32_t xrow = i < n1 ? (spr[i] ^ spr[inx]) & (r ^ rn) & jmask : 0u;
+        xm |= (uint64_t)xrow << (8 * i);
+        // P_i right of Q's edge j: the edge enters Q
+        sm |= (uint64_t)(xrow & ~spr[i]) << (8 * i);
+      }
+      inside = vertex0_inclusion<K>(P, n1, Q, n2, spr, sqr);
     }
-    const uint32_t inside = vertex0_inclusion<K>(P, n1, Q, n2, spr, sqr);
-    float B[K], L[K], W1[K], W2[K], Bq[K], M[K], V1[K], V2[K];
-    crossing_sums<K, false, BLOCK>(P, n1, Q, n2, epx, epy, xrow, erow, exact, s_q + tid,
-                                   s_acc + tid, B, L, W1, W2, Bq, M, V1, V2);
-    float ep[K], eq[K], cp[K], cq[K];
-    vertex_inclusion<K>(inside, xrow, ep, eq);
-    edge_cross<K>(P, n1, Q, n2, cp, cq);
+    forget(P);
+    forget(Q);
+    float B[K], L[K], W2[K];
+    crossing_sums<K, false, BLOCK>(P, n1, Q, n2, xm, sm, exact, s, B, L, W2);
+    reload_q(s, Q);
+    uint32_t ep, eq;
+    vertex_inclusion<K>(inside, xm, ep, eq);
     float inter = 0.f, a1 = 0.f, a2 = 0.f;
+    const float ox = P.x[0], oy = P.y[0];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       // inside fractions: the integer part (inclusion and base) plus the terms
-      inter = fmaf(cp[k], (ep[k] + B[k]) + L[k], inter);
-      inter = fmaf(cq[k], (eq[k] + Bq[k]) + M[k], inter);
-      a1 += cp[k];
-      a2 += cq[k];
+      const float cp = edge_cross<K>(P, k, n1, ox, oy), cq = edge_cross<K>(Q, k, n2, ox, oy);
+      const float2 bm = s.bm[k * BLOCK + tid];
+      inter = fmaf(cp, ((float)((ep >> k) & 1u) + B[k]) + L[k], inter);
+      inter = fmaf(cq, ((float)((eq >> k) & 1u) + bm.x) + bm.y, inter);
+      a1 += cp;
+      a2 += cq;
     }
     inter *= 0.5f;
     a1 *= 0.5f;
@@ -353,8 +419,7 @@ template <int K>
 __global__ __launch_bounds__(simple_block<K>())
 __attribute__((amdgpu_waves_per_eu(simple_waves<K>()))) void k_simple_bwd(SimpleBwdArgs args) {
   constexpr int BLOCK = simple_block<K>();
-  __shared__ float2 s_q[K * BLOCK];
-  __shared__ float4 s_acc[K * BLOCK];
+  __shared__ SimpleLds<K, true, BLOCK> s;
   const int tid = threadIdx.x;
   const int64_t n = args.a.count;
   for (int64_t p = (int64_t)blockIdx.x * BLOCK + tid; p < n; p += (int64_t)gridDim.x * BLOCK) {
@@ -363,32 +428,29 @@ __attribute__((amdgpu_waves_per_eu(simple_waves<K>()))) void k_simple_bwd(Simple
     Poly<K> P, Q;
     load_poly<K, false>(args.a.xy, p, args.a.kmax, args.a.vec4, n1, P);
     load_poly<K, false>(args.b.xy, p, args.b.kmax, args.b.vec4, n2, Q);
-    float epx[K], epy[K], eqx[K], eqy[K];
-    (void)edges<K>(P, n1, Q, n2, epx, epy, eqx, eqy);
-    const uint64_t xm = args.xmask[p], sm = args.smask[p];
+    const uint64_t xraw = args.xmask[p], sm = args.smask[p];
     const uint32_t inside = args.inside[p];
     // only the bits of real edge pairs are read, so that a mask that does not
     // fit the pair (invalid saved state) still addresses this lane's slots
-    const uint32_t jmask = (1u << n2) - 1u;
-    uint32_t xrow[K], erow[K];
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      xrow[i] = i < n1 ? (uint32_t)(xm >> (8 * i)) & jmask : 0u;
-      erow[i] = (uint32_t)(sm >> (8 * i)) & jmask;
-    }
-    float B[K], L[K], W1[K], W2[K], Bq[K], M[K], V1[K], V2[K];
-    crossing_sums<K, true, BLOCK>(P, n1, Q, n2, epx, epy, xrow, erow, false, s_q + tid, s_acc + tid,
-                                  B, L, W1, W2, Bq, M, V1, V2);
-    float ep[K], eq[K], cp[K], cq[K];
-    vertex_inclusion<K>(inside, xrow, ep, eq);
-    edge_cross<K>(P, n1, Q, n2, cp, cq);
+    const uint64_t jmask = (uint64_t)((1u << n2) - 1u) * 0x0101010101010101ull;
+    const uint64_t xm = xraw & jmask & (n1 == 8 ? ~0ull : (1ull << (8 * n1)) - 1ull);
+    float B[K], W1[K], W2[K];
+    crossing_sums<K, true, BLOCK>(P, n1, Q, n2, xm, sm & jmask, false, s, B, W1, W2);
+    reload_q(s, Q);
+    forget(P);
+    uint32_t ep, eq;
+    vertex_inclusion<K>(inside, xm, ep, eq);
     float inter = 0.f, a1 = 0.f, a2 = 0.f;
+    const float ox = P.x[0], oy = P.y[0];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      inter = fmaf(cp[k], (ep[k] + B[k]) + L[k], inter);
-      inter = fmaf(cq[k], (eq[k] + Bq[k]) + M[k], inter);
-      a1 += cp[k];
-      a2 += cq[k];
+      const float cp = edge_cross<K>(P, k, n1, ox, oy), cq = edge_cross<K>(Q, k, n2, ox, oy);
+      const float2 bv = s.bm[k * BLOCK + tid];
+      const float v2 = s.v2[k * BLOCK + tid];
+      inter = fmaf(cp, ((float)((ep >> k) & 1u) + B[k]) + (W1[k] + W2[k]), inter);
+      inter = fmaf(cq, ((float)((eq >> k) & 1u) + bv.x) + (bv.y + v2), inter);
+      a1 += cp;
+      a2 += cq;
     }
     inter *= 0.5f;
     a1 *= 0.5f;
@@ -397,59 +459,30 @@ __attribute__((amdgpu_waves_per_eu(simple_waves<K>()))) void k_simple_bwd(Simple
     // IoU = I / U: d IoU = (A1 + A2) / U^2 dI - I / U^2 (dA1 + dA2)
     const bool live = inter > 0.f && u > 0.f;
     const float ru = live ? fast_rcp(u) : 0.f;
-    const float g = args.grad[p];
+    const float g = args.grad[opaque(p)];
     const float cI = g * (a1 + a2) * ru * ru, cA = -g * inter * ru * ru;
-    // inside-part weights of each edge: W1 = int (1 - t), W2 = int t over
-    // the inside part, each half the integer part plus its terms (the same
-    // for Q's edges: V1, V2)
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      W1[k] = fmaf(0.5f, ep[k] + B[k], W1[k]);
-      W2[k] = fmaf(0.5f, ep[k] + B[k], W2[k]);
-      V1[k] = fmaf(0.5f, eq[k] + Bq[k], V1[k]);
-      V2[k] = fmaf(0.5f, eq[k] + Bq[k], V2[k]);
-    }
     float* oa = args.ga_xy + p * (int64_t)args.a.kmax * 2;
     float* ob = args.gb_xy + p * (int64_t)args.b.kmax * 2;
+    // inside-part weights of each edge: W1 = int (1 - t), W2 = int t over
+    // the inside part, each half the integer part plus its terms
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      // the edge arriving at vertex k and the vertex before k
-      const int kp = k == 0 ? n1 - 1 : k - 1;
-      float w2p = W2[0], npx = epy[0], npy = -epx[0];
-      float ppx = P.x[0], ppy = P.y[0];
-#pragma unroll
-      for (int t = 1; t < K; ++t) {
-        w2p = t == kp ? W2[t] : w2p;
-        npx = t == kp ? epy[t] : npx;
-        npy = t == kp ? -epx[t] : npy;
-        ppx = t == kp ? P.x[t] : ppx;
-        ppy = t == kp ? P.y[t] : ppy;
-      }
-      const float pnx = next_of<K, false>(P.x, k, n1), pny = next_of<K, false>(P.y, k, n1);
-      const float gx = cI * (epy[k] * W1[k] + npx * w2p) + cA * 0.5f * (pny - ppy);
-      const float gy = cI * (-epx[k] * W1[k] + npy * w2p) + cA * 0.5f * (ppx - pnx);
-      if (k < args.a.kmax)
-        *reinterpret_cast<float2*>(oa + 2 * k) = k < n1 ? make_float2(gx, gy) : make_float2(0.f, 0.f);
+      const float h = (float)((ep >> k) & 1u) + B[k];
+      W1[k] = fmaf(0.5f, h, W1[k]);
+      W2[k] = fmaf(0.5f, h, W2[k]);
     }
+    forget(P);
+    store_grad<K>(P, n1, W1, W2, cI, cA, oa, args.a.kmax, args.a.vec4);
+    // the same for Q's edges
+    reload_q(s, Q);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int kp = k == 0 ? n2 - 1 : k - 1;
-      float v2p = V2[0], npx = eqy[0], npy = -eqx[0];
-      float ppx = Q.x[0], ppy = Q.y[0];
-#pragma unroll
-      for (int t = 1; t < K; ++t) {
-        v2p = t == kp ? V2[t] : v2p;
-        npx = t == kp ? eqy[t] : npx;
-        npy = t == kp ? -eqx[t] : npy;
-        ppx = t == kp ? Q.x[t] : ppx;
-        ppy = t == kp ? Q.y[t] : ppy;
-      }
-      const float qnx = next_of<K, false>(Q.x, k, n2), qny = next_of<K, false>(Q.y, k, n2);
-      const float gx = cI * (eqy[k] * V1[k] + npx * v2p) + cA * 0.5f * (qny - ppy);
-      const float gy = cI * (-eqx[k] * V1[k] + npy * v2p) + cA * 0.5f * (ppx - qnx);
-      if (k < args.b.kmax)
-        *reinterpret_cast<float2*>(ob + 2 * k) = k < n2 ? make_float2(gx, gy) : make_float2(0.f, 0.f);
+      const float2 bv = s.bm[k * BLOCK + tid];
+      const float h = (float)((eq >> k) & 1u) + bv.x;
+      W1[k] = fmaf(0.5f, h, bv.y);
+      W2[k] = fmaf(0.5f, h, s.v2[k * BLOCK + tid]);
     }
+    store_grad<K>(Q, n2, W1, W2, cI, cA, ob, args.b.kmax, args.b.vec4);
   }
 }
 
