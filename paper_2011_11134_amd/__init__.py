@@ -14,6 +14,7 @@ import atexit
 import ctypes
 import os
 
+import numpy as np
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -169,7 +170,9 @@ def context(device=None):
 
 
 def _stream(t):
-    return torch.cuda.current_stream(t.device).cuda_stream
+    # the raw handle of torch's current stream (building torch's stream object
+    # around it takes 2 us)
+    return torch._C._cuda_getCurrentRawStream(t.device.index)
 
 
 def _ptr(t):
@@ -357,20 +360,29 @@ def iou_boxes_backward(a, b, grad, nx, xflags):
 
 class SavedPairs:
     """Device buffers of a dgal_saved work list (pairs that survived the cull
-    of a matrix forward, with their nx / xflags) and its per-tile table."""
+    of a matrix forward, with their nx / xflags) and its per-tile table.
+
+    The buffers share one allocation; each attribute (pair_id int64, nx uint8,
+    xflags uint8 [capacity, cap], count int64 [1], tile_start int64, tile_count
+    int32, tile_mask int64 [tiles, TILE_MASK_WORDS], seg_prefix int64) is a view
+    of it, made when it is first read."""
 
     def __init__(self, capacity, cap, tiles, device, tile_rows=0):
-        self.pair_id = torch.empty(capacity, dtype=torch.int64, device=device)
-        self.nx = torch.empty(capacity, dtype=torch.uint8, device=device)
-        self.xflags = torch.empty((capacity, cap), dtype=torch.uint8, device=device)
-        # reset by the forward's own kernel (graph replays included)
-        self.count = torch.empty(1, dtype=torch.int64, device=device)
-        self.tile_start = torch.empty(max(tiles, 1), dtype=torch.int64, device=device)
-        self.tile_count = torch.empty(max(tiles, 1), dtype=torch.int32, device=device)
-        self.tile_mask = torch.empty((max(tiles, 1), TILE_MASK_WORDS), dtype=torch.int64,
-                                     device=device)
-        # the segments' prefixes, written by the forward and reused by the backward
-        self.seg_prefix = torch.empty(2 * (MAX_SEGMENTS + 1), dtype=torch.int64, device=device)
+        t = max(tiles, 1)
+        n = 0
+        self._parts = parts = {}
+        for name, size in (("pair_id", 8 * capacity),
+                           # reset by the forward's own kernel (graph replays included)
+                           ("count", 8), ("tile_start", 8 * t),
+                           ("tile_mask", 8 * t * TILE_MASK_WORDS),
+                           # the segments' prefixes, written by the forward and
+                           # reused by the backward
+                           ("seg_prefix", 16 * (MAX_SEGMENTS + 1)), ("tile_count", 4 * t),
+                           ("xflags", capacity * cap), ("nx", capacity)):
+            parts[name] = (n, size)
+            n += (size + 255) & ~255
+        self._cap = cap
+        self._buf = torch.empty(n, dtype=torch.uint8, device=device)
         self.capacity = capacity
         self.tiles = tiles
         self.tiles_used = 0  # tiles of the last forward (set by iou_matrix)
@@ -378,10 +390,36 @@ class SavedPairs:
         # and records it here for the backward
         self.tile_rows = tile_rows
 
+    _DTYPES = {"pair_id": torch.int64, "count": torch.int64, "tile_start": torch.int64,
+               "tile_mask": torch.int64, "seg_prefix": torch.int64, "tile_count": torch.int32}
+
+    def __getattr__(self, name):  # only for what is not set yet
+        part = self.__dict__.get("_parts", {}).get(name)
+        if part is None:
+            raise AttributeError(name)
+        v = self._buf[part[0]:part[0] + part[1]]
+        if name in self._DTYPES:
+            v = v.view(self._DTYPES[name])
+        if name == "xflags":
+            v = v.view(self.capacity, self._cap)
+        elif name == "tile_mask":
+            v = v.view(-1, TILE_MASK_WORDS)
+        self.__dict__[name] = v
+        return v
+
+    def _at(self, name, base):
+        v = self.__dict__.get(name)  # a view, or a tensor set in its place
+        if v is not None:
+            return v.data_ptr()
+        first, size = self._parts[name]
+        return base + first if size else None  # (an empty tensor has no address)
+
     def struct(self):
-        return Saved(_ptr(self.pair_id), _ptr(self.nx), _ptr(self.xflags), self.capacity,
-                     _ptr(self.count), _ptr(self.tile_start), _ptr(self.tile_count), self.tiles,
-                     _ptr(self.tile_mask), self.tile_rows, _ptr(self.seg_prefix))
+        b = self._buf.data_ptr()
+        at = self._at
+        return Saved(at("pair_id", b), at("nx", b), at("xflags", b), self.capacity,
+                     at("count", b), at("tile_start", b), at("tile_count", b), self.tiles,
+                     at("tile_mask", b), self.tile_rows, at("seg_prefix", b))
 
 
 def segments(n_a, n_b, a_off, b_off=None, self_pairs=False, device=None):
@@ -389,32 +427,60 @@ def segments(n_a, n_b, a_off, b_off=None, self_pairs=False, device=None):
     total output size, tile capacity (the most tiles over the tile shapes),
     {tile rows: tile count}).  Build it before a HIP-graph capture and pass it as
     `seg=` (the table itself needs host-to-device copies)."""
-    dev = torch.device("cuda", torch.cuda.current_device()) if device is None else device
+    dev = torch.device("cuda", torch.cuda.current_device()) if device is None else torch.device(device)
     return _segments(n_a, n_b, a_off, b_off, self_pairs, dev)
 
 
-def _segments(n_a, n_b, a_off, b_off, self_pairs, dev):
-    """Device offsets (a_off, b_off, out_off) and total output size."""
+_TILE_R = np.array(TILE_ROWS_CHOICES)[:, None]
+_TILE_C = TILE_PAIRS // _TILE_R
+
+
+def _offsets(off):
+    """Offsets (a tensor on any device, or a sequence) as an int64 numpy array."""
+    if not (isinstance(off, torch.Tensor) and off.dtype == torch.int64 and not off.is_cuda):
+        off = torch.as_tensor(off, dtype=torch.int64).cpu()
+    return off.numpy()
+
+
+def _segments(n_a, n_b, a_off, b_off, self_pairs, dev, wait=True):
+    """Device offsets (a_off, b_off, out_off) and total output size.  The
+    three go to the device in one copy from pinned memory, on the current
+    stream (wait: and are there when this returns, for any stream)."""
     if a_off is None:
         by = {r: ((-(-n_a // r)) * (-(-n_b // (TILE_PAIRS // r))) if n_a and n_b else 0)
               for r in TILE_ROWS_CHOICES}
         return None, None, None, 0, n_a * n_b, max(by.values()), by
-    a_off = torch.as_tensor(a_off, dtype=torch.int64)
-    b_off = a_off if (self_pairs or b_off is None) else torch.as_tensor(b_off, dtype=torch.int64)
-    a_cpu, b_cpu = a_off.cpu(), b_off.cpu()
-    sizes = (a_cpu[1:] - a_cpu[:-1]) * (b_cpu[1:] - b_cpu[:-1])
-    out_off = torch.cat([torch.zeros(1, dtype=torch.int64), torch.cumsum(sizes, 0)[:-1]])
-    total = int(sizes.sum())
-    nseg = int(a_cpu.numel() - 1)
+    a_cpu = _offsets(a_off)
+    b_cpu = a_cpu if (self_pairs or b_off is None) else _offsets(b_off)
+    nseg = a_cpu.size - 1
     if not 1 <= nseg <= MAX_SEGMENTS:
         raise ValueError(f"1..{MAX_SEGMENTS} segments supported, got {nseg}")
     na = a_cpu[1:] - a_cpu[:-1]
     nb = b_cpu[1:] - b_cpu[:-1]
-    by = {r: int(torch.where(sizes > 0, ((na + r - 1) // r) *
-                             ((nb + TILE_PAIRS // r - 1) // (TILE_PAIRS // r)), 0).sum())
-          for r in TILE_ROWS_CHOICES}
-    return (a_off.to(dev).contiguous(), b_off.to(dev).contiguous(), out_off.to(dev).contiguous(),
-            nseg, total, max(by.values()), by)
+    sizes = na * nb
+    ends = sizes.cumsum()
+    total = int(ends[-1])
+    tiles = (na + _TILE_R - 1) // _TILE_R * ((nb + _TILE_C - 1) // _TILE_C)
+    by = dict(zip(TILE_ROWS_CHOICES, (tiles * (sizes > 0)).sum(1).tolist()))
+    two = b_cpu is not a_cpu
+    host = torch.empty((3 if two else 2) * (nseg + 1), dtype=torch.int64, pin_memory=True)
+    h = host.numpy()
+    h[:nseg + 1] = a_cpu
+    if two:
+        h[nseg + 1:2 * (nseg + 1)] = b_cpu
+    o = h[-(nseg + 1):]
+    o[0] = 0
+    o[1:] = ends
+    d = host.to(dev, non_blocking=not wait)
+
+    def on_device(off, view):  # offsets given on the device are used as they are
+        there = (isinstance(off, torch.Tensor) and off.is_cuda and off.dtype == torch.int64 and
+                 off.is_contiguous() and dev.index in (None, off.device.index))
+        return off if there else view
+
+    d_a = on_device(a_off, d[:nseg + 1])
+    d_b = on_device(b_off, d[nseg + 1:2 * (nseg + 1)]) if two else d_a
+    return d_a, d_b, d[-(nseg + 1):-1], nseg, total, max(by.values()), by
 
 
 def iou_matrix(a_xy, b_xy=None, a_nv=None, b_nv=None, a_z=None, b_z=None, a_off=None, b_off=None,
@@ -439,7 +505,8 @@ def iou_matrix(a_xy, b_xy=None, a_nv=None, b_nv=None, a_z=None, b_z=None, a_off=
     pb, kb = polys(b_xy, b_nv, b_z)
     dev = a_xy.device
     if seg is None:
-        seg = _segments(a_xy.shape[0], b_xy.shape[0], a_off, b_off, self_pairs, dev)
+        # (what follows on this stream comes after the copy of the offsets)
+        seg = _segments(a_xy.shape[0], b_xy.shape[0], a_off, b_off, self_pairs, dev, wait=False)
     d_a, d_b, d_o, nseg, total, tiles, tiles_by = seg
     iou = torch.empty(total, dtype=torch.float32, device=dev)
     given = saved
@@ -668,8 +735,9 @@ def path_stats(device=None):
 
 def check_errors(device=None):
     """Synchronises torch's current stream and raises on a deferred device error."""
-    dev = torch.device("cuda", torch.cuda.current_device()) if device is None else device
-    st = lib.dgal_check(context(dev), torch.cuda.current_stream(dev).cuda_stream)
+    dev = torch.device("cuda", torch.cuda.current_device()) if device is None else torch.device(device)
+    idx = dev.index if dev.index is not None else torch.cuda.current_device()
+    st = lib.dgal_check(context(dev), torch._C._cuda_getCurrentRawStream(idx))
     _ok(st, "deferred device error")
 
 

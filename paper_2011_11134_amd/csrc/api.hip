@@ -34,6 +34,7 @@ struct dgal_ctx {
   bool tune = false;
   bool validate = false;         // check every input polygon before each call
   int64_t* n_bad = nullptr;      // device counter of the input check
+  volatile int* err_host = nullptr;  // the device errors (v.err) as the host reads them
   unsigned long long* stats_dev = nullptr;  // path statistics (3 counters)
   std::string arch;              // e.g. "gfx950"
   std::map<std::string, dgal::LaunchShape> tuned;  // by TuneKey::text
@@ -62,13 +63,24 @@ std::string bucket_of(int64_t x, int64_t y = -1) {
   return y < 0 ? std::to_string(bits_of(x)) : std::to_string(bits_of(x)) + "." + std::to_string(bits_of(y));
 }
 
-// Sticky device error word: read (after the stream's work) and cleared.
+// Sticky device errors: read (after the stream's work) and cleared; bit k of
+// *out is word k.  Reading pinned host memory after one synchronisation takes
+// 4 us where a copy of a device word took 22.
 int read_err(dgal_ctx* ctx, hipStream_t stream, int* out) {
-  if (hipStreamSynchronize(stream) != hipSuccess ||
-      hipMemcpy(out, ctx->v.err, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess)
-    return DGAL_EHIP;
-  if (*out != 0 && hipMemset(ctx->v.err, 0, sizeof(int)) != hipSuccess) return DGAL_EHIP;
+  if (hipStreamSynchronize(stream) != hipSuccess) return DGAL_EHIP;
+  *out = 0;
+  for (int k = 0; k < dgal::kErrWords; ++k) {
+    if (ctx->err_host[k] == 0) continue;
+    *out |= 1 << k;
+    ctx->err_host[k] = 0;
+  }
   return DGAL_OK;
+}
+
+// Whether no call of this context can have a tuned shape: then a call needs
+// neither its key nor its candidates (1.5 us of the host's time).
+bool untuned(const dgal_ctx* ctx) {
+  return !ctx->tune && ctx->tuned.empty() && dgal::tune_store_empty();
 }
 
 // Runs launch(shape) with the shape tuned for `key`: the context's choice,
@@ -86,11 +98,11 @@ int read_err(dgal_ctx* ctx, hipStream_t stream, int* out) {
 // and the call's outputs come from one more run of it.  Tuning is skipped
 // while the error word already holds an error.  `fix` (optional) overrides
 // fields of every shape the call launches.
-template <class F, class G>
-int run_tuned(dgal_ctx* ctx, const TuneKey& key, const std::vector<dgal::LaunchShape>& cands,
-              hipStream_t stream, F launch, G fix) {
+template <class K, class C, class F, class G>
+int run_tuned(dgal_ctx* ctx, K key, C candidates, hipStream_t stream, F launch, G fix) {
   auto go = [&](dgal::LaunchShape sh) { return launch(fix(sh)); };
-  const std::string text = key.text(ctx->arch);
+  if (untuned(ctx)) return go(dgal::LaunchShape());
+  const std::string text = key().text(ctx->arch);
   auto it = ctx->tuned.find(text);
   if (it != ctx->tuned.end()) return go(it->second);
   dgal::LaunchShape stored;
@@ -102,10 +114,11 @@ int run_tuned(dgal_ctx* ctx, const TuneKey& key, const std::vector<dgal::LaunchS
   int pending = 0;
   if (int st = read_err(ctx, stream, &pending)) return st;
   if (pending != 0) {  // an earlier call's error: put it back, tune another time
-    if (hipMemcpy(ctx->v.err, &pending, sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
-      return DGAL_EHIP;
+    for (int k = 0; k < dgal::kErrWords; ++k)
+      if (pending >> k & 1) ctx->err_host[k] = 1;
     return go(dgal::LaunchShape());
   }
+  const std::vector<dgal::LaunchShape> cands = candidates();
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
     if (e0) (void)hipEventDestroy(e0);
@@ -176,10 +189,9 @@ int run_tuned(dgal_ctx* ctx, const TuneKey& key, const std::vector<dgal::LaunchS
   return go(chosen);
 }
 
-template <class F>
-int run_tuned(dgal_ctx* ctx, const TuneKey& key, const std::vector<dgal::LaunchShape>& cands,
-              hipStream_t stream, F launch) {
-  return run_tuned(ctx, key, cands, stream, launch, [](dgal::LaunchShape sh) { return sh; });
+template <class K, class C, class F>
+int run_tuned(dgal_ctx* ctx, K key, C candidates, hipStream_t stream, F launch) {
+  return run_tuned(ctx, key, candidates, stream, launch, [](dgal::LaunchShape sh) { return sh; });
 }
 
 std::vector<dgal::LaunchShape> pair_grids(int cus) {
@@ -283,8 +295,14 @@ int dgal_create(dgal_ctx** out, int hip_device) {
       cus <= 0)
     cus = 256;
   c->v.cus = cus;
-  if (hipMalloc(reinterpret_cast<void**>(&c->v.err), sizeof(int)) != hipSuccess ||
-      hipMemset(c->v.err, 0, sizeof(int)) != hipSuccess ||
+  void* err_host = nullptr;
+  if (hipHostMalloc(&err_host, dgal::kErrWords * sizeof(int),
+                    hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
+    c->err_host = static_cast<int*>(err_host);
+    for (int k = 0; k < dgal::kErrWords; ++k) c->err_host[k] = 0;
+  }
+  if (err_host == nullptr ||
+      hipHostGetDevicePointer(reinterpret_cast<void**>(&c->v.err), err_host, 0) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&c->v.prefix), sizeof(int64_t) * 2 * (DGAL_MAX_SEGMENTS + 1)) !=
           hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&c->v.scan), sizeof(int64_t) * dgal::kScanTotals) !=
@@ -295,7 +313,7 @@ int dgal_create(dgal_ctx** out, int hip_device) {
       hipMemset(c->stats_dev, 0, 3 * sizeof(unsigned long long)) != hipSuccess ||
       hipDeviceSynchronize() != hipSuccess) {
     if (c->stats_dev) (void)hipFree(c->stats_dev);
-    if (c->v.err) (void)hipFree(c->v.err);
+    if (err_host) (void)hipHostFree(err_host);
     if (c->v.prefix) (void)hipFree(c->v.prefix);
     if (c->v.scan) (void)hipFree(c->v.scan);
     if (c->n_bad) (void)hipFree(c->n_bad);
@@ -305,7 +323,7 @@ int dgal_create(dgal_ctx** out, int hip_device) {
   // the allocation-free matrix forward's static scratch: its address on this
   // device, taken once per device (here, with the device current)
   if (dgal::matrix_scratch_init(hip_device) != DGAL_OK) {
-    (void)hipFree(c->v.err);
+    (void)hipHostFree(err_host);
     (void)hipFree(c->v.prefix);
     (void)hipFree(c->v.scan);
     (void)hipFree(c->n_bad);
@@ -332,7 +350,7 @@ void dgal_destroy(dgal_ctx* ctx) {
   DeviceGuard g(ctx->v.device);
   if (ctx->prof.e0) (void)hipEventDestroy(ctx->prof.e0);
   if (ctx->prof.e1) (void)hipEventDestroy(ctx->prof.e1);
-  if (ctx->v.err) (void)hipFree(ctx->v.err);
+  if (ctx->err_host) (void)hipHostFree(const_cast<int*>(ctx->err_host));
   if (ctx->v.prefix) (void)hipFree(ctx->v.prefix);
   if (ctx->v.scan) (void)hipFree(ctx->v.scan);
   if (ctx->n_bad) (void)hipFree(ctx->n_bad);
@@ -355,16 +373,10 @@ int dgal_check(dgal_ctx* ctx, void* stream) {
   if (ctx == nullptr) return DGAL_EINVAL;
   DeviceGuard g(ctx->v.device);
   if (!g.ok) return DGAL_EHIP;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  if (hipStreamSynchronize(s) != hipSuccess) return DGAL_EHIP;
-  int host = 0;
-  if (hipMemcpy(&host, ctx->v.err, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess) return DGAL_EHIP;
-  if (host != 0) {
-    if (hipMemset(ctx->v.err, 0, sizeof(int)) != hipSuccess) return DGAL_EHIP;
-    if (host & dgal::kErrCapacity) return DGAL_ECAPACITY;
-    return DGAL_EINVAL;
-  }
-  return DGAL_OK;
+  int errs = 0;
+  if (int st = read_err(ctx, static_cast<hipStream_t>(stream), &errs)) return st;
+  if (errs >> dgal::kErrCapacity & 1) return DGAL_ECAPACITY;
+  return errs != 0 ? DGAL_EINVAL : DGAL_OK;
 }
 
 int dgal_iou_pairs(dgal_ctx* ctx, dgal_polys a, dgal_polys b, float* iou, uint8_t* nx,
@@ -394,8 +406,8 @@ int dgal_iou_pairs(dgal_ctx* ctx, dgal_polys a, dgal_polys b, float* iou, uint8_
                      args.a.vec4 && args.b.vec4 && (nx == nullptr || args.flags_vec);
   const bool z3 = a.zlo != nullptr, save = nx != nullptr;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const TuneKey key{kTunePairsFwd, K, fixed, z3, save, bucket_of(a.count)};
-  return run_tuned(ctx, key, pair_grids(ctx->v.cus), s,
+  auto key = [&] { return TuneKey{kTunePairsFwd, K, fixed, z3, save, bucket_of(a.count)}; };
+  return run_tuned(ctx, key, [&] { return pair_grids(ctx->v.cus); }, s,
                    [&](const dgal::LaunchShape& sh) {
                      dgal::prof_begin(ctx->v.prof, s);
                      const hipError_t e = dgal::launch_pairs_fwd(args, K, fixed, z3, save, s, sh);
@@ -451,8 +463,8 @@ int dgal_iou_backward(dgal_ctx* ctx, int32_t mode, dgal_polys a, dgal_polys b,
     const bool fixed = a.nv == nullptr && b.nv == nullptr && a.kmax == K && b.kmax == K &&
                        args.a.vec4 && args.b.vec4 && args.flags_vec;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const TuneKey key{kTunePairsBwd, K, fixed, z3, 0, bucket_of(a.count)};
-    return run_tuned(ctx, key, pair_grids(ctx->v.cus), s,
+    auto key = [&] { return TuneKey{kTunePairsBwd, K, fixed, z3, 0, bucket_of(a.count)}; };
+    return run_tuned(ctx, key, [&] { return pair_grids(ctx->v.cus); }, s,
                      [&](const dgal::LaunchShape& sh) {
                        dgal::prof_begin(ctx->v.prof, s);
                        const hipError_t e = dgal::launch_pairs_bwd(args, K, fixed, z3, s, sh);
@@ -462,8 +474,8 @@ int dgal_iou_backward(dgal_ctx* ctx, int32_t mode, dgal_polys a, dgal_polys b,
   }
   if (mode == DGAL_MATRIX) {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const TuneKey key = matrix_key(kTuneMatrixBwd, a, b, a_off, nseg);
-    return run_tuned(ctx, key, matrix_bwd_shapes(), s, [&](const dgal::LaunchShape& sh) {
+    auto key = [&] { return matrix_key(kTuneMatrixBwd, a, b, a_off, nseg); };
+    return run_tuned(ctx, key, matrix_bwd_shapes, s, [&](const dgal::LaunchShape& sh) {
       return dgal::matrix_backward(ctx->v, a, b, a_off, b_off, out_off, nseg, self_pairs,
                                    grad_iou, out_size, saved, grad_a_xy, grad_b_xy, grad_a_z,
                                    grad_b_z, s, sh);
@@ -482,9 +494,9 @@ int dgal_iou_matrix(dgal_ctx* ctx, dgal_polys a, dgal_polys b, const int64_t* a_
   if (rows != 0 && rows != 4 && rows != 8 && rows != 16) return DGAL_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (int st = debug_validate(ctx, s, a, dgal::same_polys(a, b) ? nullptr : &b)) return st;
-  const TuneKey key = matrix_key(kTuneMatrixFwd, a, b, a_off, nseg);
+  auto key = [&] { return matrix_key(kTuneMatrixFwd, a, b, a_off, nseg); };
   return run_tuned(
-      ctx, key, matrix_fwd_shapes(rows), s,
+      ctx, key, [&] { return matrix_fwd_shapes(rows); }, s,
       [&](const dgal::LaunchShape& sh) {
         return dgal::matrix_forward(ctx->v, a, b, a_off, b_off, out_off, nseg, self_pairs, iou,
                                     out_size, saved, s, sh);
@@ -504,11 +516,13 @@ int dgal_iou_matrix_noalloc(dgal_ctx* ctx, dgal_polys a, dgal_polys b, const int
   // a shape the autotuner already chose for dgal_iou_matrix (in this context,
   // or in the process-wide store) is reused; nothing is tuned here (tuning
   // allocates events and records its choice)
-  const std::string key = matrix_key(kTuneMatrixFwd, a, b, a_off, nseg).text(ctx->arch);
   dgal::LaunchShape shape;
-  const auto it = ctx->tuned.find(key);
-  if (it != ctx->tuned.end()) shape = it->second;
-  else if (!dgal::tune_store_get(key, &shape) || !dgal::shape_valid(shape)) shape = dgal::LaunchShape();
+  if (!untuned(ctx)) {
+    const std::string key = matrix_key(kTuneMatrixFwd, a, b, a_off, nseg).text(ctx->arch);
+    const auto it = ctx->tuned.find(key);
+    if (it != ctx->tuned.end()) shape = it->second;
+    else if (!dgal::tune_store_get(key, &shape) || !dgal::shape_valid(shape)) shape = dgal::LaunchShape();
+  }
   return dgal::matrix_forward_noalloc(ctx->v, a, b, a_off, b_off, out_off, nseg, self_pairs, iou,
                                       out_size, s, shape);
 }

@@ -89,7 +89,7 @@ __global__ __launch_bounds__(kBoxBlock) void k_boxes_fwd(BoxesFwdArgs args) {
     }
     args.iou[i] = Z3 ? iou_3d(r.inter, r.a1, r.a2, r.m, zl1, zh1, zl2, zh2)
                      : iou_2d(r.inter, r.a1, r.a2, r.m);
-    if (r.overflow) atomicOr(args.err, kErrCapacity);
+    if (r.overflow) raise_error(args.err, kErrCapacity);
     if (SAVE) {
       args.nx[i] = (uint8_t)r.m;
       *reinterpret_cast<uint2*>(args.xflags + i * CAP) = make_uint2(r.codes[0], r.codes[1]);

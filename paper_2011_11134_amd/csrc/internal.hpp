@@ -9,8 +9,14 @@
 
 namespace dgal {
 
-// Bits of the sticky device error word.
-enum : int { kErrCapacity = 1, kErrSegment = 2 };
+// The sticky device errors: one word of pinned host memory each, which a
+// kernel sets with a plain store (an atomic or does not cross the bus), so that
+// a check reads them after its stream's work without a copy.
+enum : int { kErrCapacity = 0, kErrSegment = 1, kErrWords = 2 };
+
+__device__ __forceinline__ void raise_error(int* err, int which) {
+  __hip_atomic_store(err + which, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 struct PolyArgs {
   const float* xy;
@@ -150,7 +156,7 @@ inline void prof_end(Profiler* p, const char* name, hipStream_t s) {
 struct CtxView {
   int device;
   int cus;          // compute units of the device
-  int* err;         // sticky device error word
+  int* err;         // [kErrWords] sticky device errors (device address)
   int64_t* prefix;  // [2][DGAL_MAX_SEGMENTS + 1]: tile and row-group prefixes
   int64_t* scan;    // [kScanTotals]: per-chunk totals of the tile scan
   Profiler* prof;   // per-kernel timing, or NULL

@@ -130,7 +130,7 @@ __global__ __launch_bounds__(256) void k_seg_prep(SegArgs a, int* err, int64_t* 
   for (int s = s0; s < s1; ++s) {
     const Segment g = load_segment(a, s);
     if (!g.ok) {
-      atomicOr(err, kErrSegment);
+      raise_error(err, kErrSegment);
       continue;
     }
     sg += groups_of(g);
@@ -355,7 +355,7 @@ __device__ __forceinline__ void write_prefixes(const CullArgs& m, SegScan& sc) {
   for (int s = s0; s < s1; ++s) {
     const Segment g = load_segment(a, s);
     if (g.ok) v += groups_of(g);
-    else atomicOr(m.err, kErrSegment);
+    else raise_error(m.err, kErrSegment);
     const int64_t next = s + 1 < a.nseg ? a.out_off[s + 1] : g.out0 + g.na * g.nb;
     dense = dense && g.ok && next == g.out0 + g.na * g.nb && (s > 0 || g.out0 == 0);
   }
@@ -603,7 +603,7 @@ __device__ __forceinline__ void mask_unit(const CullArgs& m, const Segment& g, i
       state[kBitWords] = (uint64_t)(g.out0 + row * g.nb + cb);
       state[kBitWords + 1] = (uint64_t)g.nb;
     } else {
-      atomicOr(m.err, kErrCapacity);
+      raise_error(m.err, kErrCapacity);
     }
   }
 }
@@ -869,7 +869,7 @@ __global__ __launch_bounds__(kListBlock) void k_matrix_list(ListArgs m) {
   }
   if (t1 == nt && tid == 0) {
     *m.count = run;
-    if (run > m.capacity) atomicOr(m.err, kErrCapacity);
+    if (run > m.capacity) raise_error(m.err, kErrCapacity);
   }
 }
 struct ExactArgs {
@@ -990,7 +990,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_matrix_exact(ExactArgs m) {
     count_path(m.stats, res.exact, res.thin);
     m.iou[pid] = pair_iou<Z3>(res.inter, res.a1, res.a2, res.m, m.a.zlo, m.a.zhi, ia, m.b.zlo,
                               m.b.zhi, ib);
-    if (res.overflow) atomicOr(m.err, kErrCapacity);
+    if (res.overflow) raise_error(m.err, kErrCapacity);
     m.s_nx[e] = (uint8_t)res.m;
     uint8_t* row = m.s_flags + e * (int64_t)m.cap;
 #pragma unroll

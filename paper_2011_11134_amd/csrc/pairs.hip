@@ -32,7 +32,7 @@ __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<K>()))) void k_pairs_fwd(P
     count_path(args.stats, r.exact, r.thin);
     args.iou[i] = pair_iou<Z3>(r.inter, r.a1, r.a2, r.m, args.a.zlo, args.a.zhi, i, args.b.zlo,
                                args.b.zhi, i);
-    if (r.overflow) atomicOr(args.err, kErrCapacity);
+    if (r.overflow) raise_error(args.err, kErrCapacity);
     if (SAVE) {
       args.nx[i] = (uint8_t)r.m;
       uint8_t* row = args.xflags + i * (int64_t)args.cap;

@@ -33,7 +33,7 @@ __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<K>()))) void k_intersect_f
     float2 ov[CAP];
     pair_forward<K, FIXED, BLOCK, true>(P, n1, Q, n2, s_pt + tid, s_cd + tid, r, ov);
     count_path(args.stats, r.exact, false);  // vertices only: no areas to rebuild
-    if (r.overflow) atomicOr(args.err, kErrCapacity);
+    if (r.overflow) raise_error(args.err, kErrCapacity);
     args.nx[i] = (uint8_t)r.m;
     uint8_t* row = args.xflags + i * (int64_t)args.cap;
     float2* out = reinterpret_cast<float2*>(args.out_xy) + i * (int64_t)args.cap;

@@ -13,6 +13,7 @@
 #include <string.h>
 #include <unistd.h>
 
+#include <atomic>
 #include <map>
 #include <mutex>
 #include <utility>
@@ -30,6 +31,7 @@ struct Entry {
 };
 
 std::mutex store_mu;
+std::atomic<bool> store_empty{true};
 std::map<std::string, Entry>& store() {
   static std::map<std::string, Entry>* m = new std::map<std::string, Entry>();
   return *m;
@@ -236,12 +238,16 @@ void tune_store_put(const std::string& key, const LaunchShape& s, double ms) {
   Entry& e = store()[key];
   e.shape = s;
   e.ms = ms;
+  store_empty = false;
 }
 
 void tune_store_clear() {
   std::lock_guard<std::mutex> lock(store_mu);
   store().clear();
+  store_empty = true;
 }
+
+bool tune_store_empty() { return store_empty; }
 
 int64_t tune_store_size() {
   std::lock_guard<std::mutex> lock(store_mu);
@@ -304,6 +310,7 @@ int tune_store_load(const char* path) {
   }
   std::lock_guard<std::mutex> lock(store_mu);
   for (auto& kv : got) store()[kv.first] = kv.second;
+  if (!got.empty()) store_empty = false;
   return (int)got.size();
 }
 

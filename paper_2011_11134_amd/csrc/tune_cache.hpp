@@ -33,6 +33,9 @@ bool tune_store_get(const std::string& key, LaunchShape* out);
 void tune_store_put(const std::string& key, const LaunchShape& s, double ms);
 void tune_store_clear();
 int64_t tune_store_size();
+// Whether the store holds nothing, without its lock (a call that finds it so
+// and does not tune needs no key).
+bool tune_store_empty();
 
 // Merges the entries of a JSON cache file into the store (a file entry
 // replaces the store's entry of the same key).  Returns the number of entries

@@ -110,3 +110,30 @@ def test_blocks_with_gaps(dg, nseg, self_pairs, shift):
     assert (got[~inside] == -7.0).all() and (buf[:shift] == -7.0).all()
     assert (buf[shift + total:] == -7.0).all()
     _check_matrix_exact(got[inside], a, b, a_off=a_off, b_off=b_off, self_pairs=self_pairs)
+
+
+@pytest.mark.parametrize("nseg", [1, 7, 4096])
+def test_segment_table_forms(dg, nseg):
+    """The segment table is the same for offsets given as a list, an array, a
+    host tensor of either width or a device tensor (then used as it is), and an
+    empty work list is refused."""
+    rng = np.random.default_rng(nseg)
+    na, nb = rng.integers(0, 600, nseg), rng.integers(0, 600, nseg)
+    off = lambda n: np.concatenate([[0], np.cumsum(n)]).astype(np.int64)
+    a, b = off(na), off(nb)
+    size = na * nb
+    tiles = {r: int((-(-na // r) * -(-nb // (2048 // r))).sum()) for r in dg.TILE_ROWS_CHOICES}
+    for form in (list, np.asarray, torch.tensor, lambda v: torch.tensor(v).int(),
+                 lambda v: torch.tensor(v).cuda()):
+        fa, fb = form(a), form(b)
+        d_a, d_b, d_o, n, total, most, by = dg.segments(int(a[-1]), int(b[-1]), fa, fb)
+        assert (n, total, most, by) == (nseg, int(size.sum()), max(tiles.values()), tiles)
+        for got, want in ((d_a, a), (d_b, b), (d_o, off(size)[:-1])):
+            assert got.is_cuda and got.dtype == torch.int64 and got.is_contiguous()
+            assert np.array_equal(got.cpu().numpy(), want)
+        if isinstance(fa, torch.Tensor) and fa.is_cuda:
+            assert d_a.data_ptr() == fa.data_ptr() and d_b.data_ptr() == fb.data_ptr()
+    xy = dev_t(_boxes(rng, 9, 5.0))
+    with pytest.raises(dg.DgalError) as e:
+        dg.iou_matrix(xy, xy, capacity=0)
+    assert e.value.status == dg.DGAL_EINVAL
