@@ -150,6 +150,48 @@ __device__ __forceinline__ double orient64(float ax, float ay, float bx, float b
   return ux * vy - uy * vx;
 }
 
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Exact sign tables of the 8-slot pairs of the lanes in `need`, by the whole
+// wavefront (every lane must be active): lane 8 i + j evaluates the (i, j)
+// entries in fp64, and a ballot is the table's word; exact zeros take the sign
+// of Q moved by (eps, eps^2).  p_col / q_col: slot 0 of the wavefront's lane 0
+// in the [8][BLOCK] LDS columns where those lanes have staged their polygons.
+// negp, negq: bit 8 i + j set when the value is negative, as the fp32 table's.
+// One lane of a wavefront needs this on 8% of the wavefronts of the 3..8-gon
+// workload; walking its 64 entries in that lane alone took 10 us, which
+// ended every launch of one round (262,144 pairs: 38 us, 25.7 now).
+template <int BLOCK>
+__device__ __forceinline__ void exact_signs8(uint64_t need, const float2* p_col,
+                                             const float2* q_col, int n1, int n2, uint64_t& negp,
+                                             uint64_t& negq) {
+  const int lane = threadIdx.x & 63, i = lane >> 3, j = lane & 7;
+  while (need != 0ull) {  // uniform
+    const int l = __builtin_ctzll(need);
+    need &= need - 1ull;
+    const int m1 = __builtin_amdgcn_readlane(n1, l), m2 = __builtin_amdgcn_readlane(n2, l);
+    const int in = i + 1 < m1 ? i + 1 : 0, jn = j + 1 < m2 ? j + 1 : 0;
+    const float2 p = p_col[i * BLOCK + l], pn = p_col[in * BLOCK + l];
+    const float2 q = q_col[j * BLOCK + l], qn = q_col[jn * BLOCK + l];
+    // orient(Q_j + d, Q_j1 + d, P_i) = o + f.y*eps - f.x*eps^2
+    const bool tie_q = (qn.y != q.y) ? (qn.y > q.y) : (q.x > qn.x);
+    // orient(P_i, P_i1, Q_j + d) = o - e.y*eps + e.x*eps^2
+    const bool tie_p = (p.y != pn.y) ? (p.y > pn.y) : (pn.x > p.x);
+    const double op = orient64(q.x, q.y, qn.x, qn.y, p.x, p.y);
+    const double oq = orient64(p.x, p.y, pn.x, pn.y, q.x, q.y);
+    const uint64_t mp = __ballot(!(op > 0.0 || (op == 0.0 && tie_q)));
+    const uint64_t mq = __ballot(!(oq > 0.0 || (oq == 0.0 && tie_p)));
+    if (lane == l) {
+      negp = mp;
+      negq = mq;
+    }
+  }
+}
+
 // Result of one pair's forward.
 template <int K>
 struct PairResult {
@@ -184,6 +226,22 @@ __device__ __forceinline__ int64_t opaque(int64_t i) {
   return i;
 }
 
+// The grid-stride walk of an elementwise forward over n > 0 pairs: at K = 8 a
+// wavefront stays whole (exact_signs8), its lanes past the end repeating the
+// last pair with live() false; else those lanes leave.
+template <int K, int BLOCK>
+struct PairLoop {
+  int64_t i, n;
+  __device__ __forceinline__ explicit PairLoop(int64_t count)
+      : i((int64_t)blockIdx.x * BLOCK + threadIdx.x), n(count) {}
+  __device__ __forceinline__ bool more() const {
+    return K == 8 ? i - (int64_t)(threadIdx.x & 63) < n : i < n;
+  }
+  __device__ __forceinline__ int64_t index() const { return K == 8 && i >= n ? n - 1 : i; }
+  __device__ __forceinline__ bool live() const { return K != 8 || i < n; }
+  __device__ __forceinline__ void next() { i += (int64_t)gridDim.x * BLOCK; }
+};
+
 // Waves per SIMD that the LDS of a pair_forward kernel allows at K = 8
 // (144 bytes a lane against 160 KiB a CU); the register allocator is held
 // to the same count (at most 128 VGPRs, met without spilling; left alone it
@@ -198,12 +256,14 @@ constexpr int fwd_waves_per_simd() {
 // [2K][BLOCK] LDS buffers (element stride BLOCK): a point, and its code with,
 // in the high byte, the edge the intersection's boundary leaves it on.  EMIT: the ordered
 // intersection vertices are also returned in ov[0..2K) (absolute frame,
-// slots at and past the vertex count set to 0).
+// slots at and past the vertex count set to 0).  At K = 8 every lane of the
+// wavefront calls it together (exact_signs8); `live` says which lanes' results
+// are used.
 template <int K, bool FIXED, int BLOCK, bool EMIT = false>
 __device__ __forceinline__ void pair_forward(const Poly<K>& P, int n1, const Poly<K>& Q, int n2,
                                              float2* __restrict__ s_pt,
                                              uint16_t* __restrict__ s_cd, PairResult<K>& res,
-                                             float2* ov = nullptr) {
+                                             float2* ov = nullptr, bool live = true) {
   constexpr int CAP = 2 * K;
   constexpr int NW = (K * K + 31) / 32;  // 32-bit words of a K x K sign table
   constexpr uint32_t KM = (1u << K) - 1u;
@@ -258,7 +318,27 @@ __device__ __forceinline__ void pair_forward(const Poly<K>& P, int n1, const Pol
   }
   const bool exact = !(omin > kCertify * E * D);
   res.exact = exact;
-  if (exact) {
+  if constexpr (K == 8) {
+    const uint64_t need = __ballot(exact && live);
+    if (need != 0ull) {  // uniform
+      if (exact) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          s_pt[k * BLOCK] = make_float2(P.x[k], P.y[k]);
+          s_pt[(K + k) * BLOCK] = make_float2(Q.x[k], Q.y[k]);
+        }
+      }
+      wave_sync();
+      uint64_t mp = (uint64_t)negp[1] << 32 | negp[0], mq = (uint64_t)negq[1] << 32 | negq[0];
+      const float2* col = s_pt - (threadIdx.x & 63);
+      exact_signs8<BLOCK>(need, col, col + K * BLOCK, n1, n2, mp, mq);
+      wave_sync();  // the columns are the points' again
+      negp[0] = (uint32_t)mp;
+      negp[1] = (uint32_t)(mp >> 32);
+      negq[0] = (uint32_t)mq;
+      negq[1] = (uint32_t)(mq >> 32);
+    }
+  } else if (exact) {
     // Exact signs in fp64; exact zeros take the sign of Q moved by (eps,
     // eps^2).  Rare, so it is written for few registers rather than speed:
     // Q is staged in this lane's (still unused) LDS column and each row of

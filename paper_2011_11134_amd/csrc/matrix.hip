@@ -222,12 +222,6 @@ __device__ __forceinline__ float lane_bcast(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 struct CullArgs {
   SegArgs seg;
   PolyArgs a, b;
@@ -968,12 +962,19 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_matrix_exact(ExactArgs m) {
   constexpr bool PREFETCH = K == 4;
   int64_t pid_next = 0;
   if (PREFETCH && wid * per + (tid & 63) < e_end) pid_next = m.pair_id[wid * per + (tid & 63)];
-  for (int64_t e = wid * per + (tid & 63); e < e_end; e += 64) {
-    const int64_t pid = PREFETCH ? pid_next : m.pair_id[e];
+  // (at K = 8 wavefronts stay whole for the pair forward: lanes without an
+  // entry repeat the wavefront's last one, and their results are dropped)
+  for (int64_t e = wid * per + (tid & 63); K == 8 ? e - (tid & 63) < e_end : e < e_end; e += 64) {
+    bool live = K != 8 || e < e_end;
+    const int64_t pid = PREFETCH ? pid_next : m.pair_id[live ? e : e_end - 1];
     if (PREFETCH && e + 64 < e_end) pid_next = m.pair_id[e + 64];
     Segment g;
     int64_t r = 0, c = 0;
-    if (!locate(m.seg, pid, sc, g, r, c)) continue;  // not written by the cull on these shapes
+    if (!locate(m.seg, pid, sc, g, r, c)) {  // not written by the cull on these shapes
+      if (K != 8) continue;
+      live = false;
+      g.a0 = g.b0 = r = c = 0;
+    }
     int64_t ia = g.a0 + r, ib = g.b0 + c;
     if (m.seg.self_pairs && r > c) {  // one unordered pair: the lower index is P
       const int64_t t = ia;
@@ -986,7 +987,8 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_matrix_exact(ExactArgs m) {
     load_poly<K, FIXED>(m.a.xy, ia, m.a.kmax, m.a.vec4, n1, P);
     load_poly<K, FIXED>(m.b.xy, ib, m.b.kmax, m.b.vec4, n2, Q);
     PairResult<K> res;
-    pair_forward<K, FIXED, kExactBlock>(P, n1, Q, n2, s_pt + tid, s_cd + tid, res);
+    pair_forward<K, FIXED, kExactBlock>(P, n1, Q, n2, s_pt + tid, s_cd + tid, res, nullptr, live);
+    if (!live) continue;
     count_path(m.stats, res.exact, res.thin);
     m.iou[pid] = pair_iou<Z3>(res.inter, res.a1, res.a2, res.m, m.a.zlo, m.a.zhi, ia, m.b.zlo,
                               m.b.zhi, ib);

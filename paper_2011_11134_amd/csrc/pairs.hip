@@ -21,14 +21,16 @@ __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<K>()))) void k_pairs_fwd(P
   __shared__ uint16_t s_cd[CAP * BLOCK];
   const int tid = threadIdx.x;
   const int64_t n = args.a.count;
-  for (int64_t i = (int64_t)blockIdx.x * BLOCK + tid; i < n; i += (int64_t)gridDim.x * BLOCK) {
+  for (PairLoop<K, BLOCK> it(n); it.more(); it.next()) {
+    const int64_t i = it.index();
     const int n1 = FIXED ? K : poly_count(args.a.nv, i, args.a.kmax);
     const int n2 = FIXED ? K : poly_count(args.b.nv, i, args.b.kmax);
     Poly<K> P, Q;
     load_poly<K, FIXED>(args.a.xy, i, args.a.kmax, args.a.vec4, n1, P);
     load_poly<K, FIXED>(args.b.xy, i, args.b.kmax, args.b.vec4, n2, Q);
     PairResult<K> r;
-    pair_forward<K, FIXED, BLOCK>(P, n1, Q, n2, s_pt + tid, s_cd + tid, r);
+    pair_forward<K, FIXED, BLOCK>(P, n1, Q, n2, s_pt + tid, s_cd + tid, r, nullptr, it.live());
+    if (!it.live()) continue;
     count_path(args.stats, r.exact, r.thin);
     args.iou[i] = pair_iou<Z3>(r.inter, r.a1, r.a2, r.m, args.a.zlo, args.a.zhi, i, args.b.zlo,
                                args.b.zhi, i);

@@ -23,7 +23,8 @@ __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<K>()))) void k_intersect_f
   __shared__ uint16_t s_cd[CAP * BLOCK];
   const int tid = threadIdx.x;
   const int64_t n = args.a.count;
-  for (int64_t i = (int64_t)blockIdx.x * BLOCK + tid; i < n; i += (int64_t)gridDim.x * BLOCK) {
+  for (PairLoop<K, BLOCK> it(n); it.more(); it.next()) {
+    const int64_t i = it.index();
     const int n1 = FIXED ? K : poly_count(args.a.nv, i, args.a.kmax);
     const int n2 = FIXED ? K : poly_count(args.b.nv, i, args.b.kmax);
     Poly<K> P, Q;
@@ -31,7 +32,8 @@ __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<K>()))) void k_intersect_f
     load_poly<K, FIXED>(args.b.xy, i, args.b.kmax, args.b.vec4, n2, Q);
     PairResult<K> r;
     float2 ov[CAP];
-    pair_forward<K, FIXED, BLOCK, true>(P, n1, Q, n2, s_pt + tid, s_cd + tid, r, ov);
+    pair_forward<K, FIXED, BLOCK, true>(P, n1, Q, n2, s_pt + tid, s_cd + tid, r, ov, it.live());
+    if (!it.live()) continue;
     count_path(args.stats, r.exact, false);  // vertices only: no areas to rebuild
     if (r.overflow) raise_error(args.err, kErrCapacity);
     args.nx[i] = (uint8_t)r.m;

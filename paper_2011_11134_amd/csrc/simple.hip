@@ -39,7 +39,8 @@ constexpr int simple_block() {
 // bytes of LDS a lane against 160 KiB a CU, and at most 128 VGPRs, so that
 // 262,144 pairs (4,096 wavefronts) are one round.  Three waves per SIMD (192
 // bytes; 168 VGPRs and 40 bytes a lane of spills in the backward) took two
-// rounds (forward 32 us, backward 46 us there, now 28.5 and 23).
+// rounds (forward 32 us, backward 46 us there; 28.5 and 23 in one, the forward
+// 20 with the exact signs taken by whole wavefronts).
 template <int K>
 constexpr int simple_waves() {
   return K == 8 ? 4 : 1;
@@ -55,13 +56,14 @@ __device__ __forceinline__ void forget(Poly<K>& P) {
 
 // Row masks of the tie-ruled sign table: bit j of spr[i] when P_i is strictly
 // left of Q's edge j, bit j of sqr[i] when Q_j is strictly left of P's edge i.
-// Returns true when the lane took the exact fp64 branch.
+// Returns true when the lane's signs are the exact fp64 ones.  s_p, s_q: the
+// lane's columns of two [K][BLOCK] LDS buffers (s_p used at K = 8).
 template <int K, int BLOCK>
 __device__ __forceinline__ bool sign_rows(const Poly<K>& P, int n1, const Poly<K>& Q, int n2,
                                           const float (&epx)[K], const float (&epy)[K],
                                           const float (&eqx)[K], const float (&eqy)[K], float E,
-                                          float2* __restrict__ s_q, uint32_t (&spr)[K],
-                                          uint32_t (&sqr)[K]) {
+                                          float2* __restrict__ s_p, float2* __restrict__ s_q,
+                                          bool live, uint32_t (&spr)[K], uint32_t (&sqr)[K]) {
   constexpr uint32_t KM = (1u << K) - 1u;
   float D = 0.f, omin = __builtin_inff();
 #pragma unroll
@@ -82,7 +84,33 @@ __device__ __forceinline__ bool sign_rows(const Poly<K>& P, int n1, const Poly<K
     sqr[i] = ~wq & KM;
   }
   const bool exact = !(omin > kCertify * E * D);
-  if (exact) {
+  if constexpr (K == 8) {  // by the whole wavefront
+    const uint64_t need = __ballot(exact && live);
+    if (need != 0ull) {  // uniform
+      if (exact) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          s_p[k * BLOCK] = make_float2(P.x[k], P.y[k]);
+          s_q[k * BLOCK] = make_float2(Q.x[k], Q.y[k]);
+        }
+      }
+      wave_sync();
+      uint64_t mp = 0ull, mq = 0ull;
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        mp |= (uint64_t)(~spr[i] & KM) << (8 * i);
+        mq |= (uint64_t)(~sqr[i] & KM) << (8 * i);
+      }
+      const int lane = threadIdx.x & 63;
+      exact_signs8<BLOCK>(need, s_p - lane, s_q - lane, n1, n2, mp, mq);
+      wave_sync();
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        spr[i] = ~(uint32_t)(mp >> (8 * i)) & KM;
+        sqr[i] = ~(uint32_t)(mq >> (8 * i)) & KM;
+      }
+    }
+  } else if (exact) {
     // exact signs in fp64; exact zeros take the sign of Q moved by (eps, eps^2)
 #pragma unroll
     for (int k = 0; k < K; ++k) s_q[k * BLOCK] = make_float2(Q.x[k], Q.y[k]);
@@ -355,7 +383,8 @@ __attribute__((amdgpu_waves_per_eu(simple_waves<K>()))) void k_simple_fwd(Simple
   __shared__ SimpleLds<K, false, BLOCK> s;
   const int tid = threadIdx.x;
   const int64_t n = args.a.count;
-  for (int64_t p = (int64_t)blockIdx.x * BLOCK + tid; p < n; p += (int64_t)gridDim.x * BLOCK) {
+  for (PairLoop<K, BLOCK> it(n); it.more(); it.next()) {
+    const int64_t p = it.index();
     const int n1 = poly_count(args.a.nv, p, args.a.kmax);
     const int n2 = poly_count(args.b.nv, p, args.b.kmax);
     Poly<K> P, Q;
@@ -368,7 +397,8 @@ __attribute__((amdgpu_waves_per_eu(simple_waves<K>()))) void k_simple_fwd(Simple
       float epx[K], epy[K], eqx[K], eqy[K];
       const float E = edges<K>(P, n1, Q, n2, epx, epy, eqx, eqy);
       uint32_t spr[K], sqr[K];
-      exact = sign_rows<K, BLOCK>(P, n1, Q, n2, epx, epy, eqx, eqy, E, s.q + tid, spr, sqr);
+      exact = sign_rows<K, BLOCK>(P, n1, Q, n2, epx, epy, eqx, eqy, E, s.bm + tid, s.q + tid,
+                                  it.live(), spr, sqr);
       // crossings: rows i and i+1 of spr differ at j, bits j and j+1 of sqr[i] differ
       const uint32_t jmask = (1u << n2) - 1u;
 #pragma unroll
@@ -383,6 +413,7 @@ __attribute__((amdgpu_waves_per_eu(simple_waves<K>()))) void k_simple_fwd(Simple
       }
       inside = vertex0_inclusion<K>(P, n1, Q, n2, spr, sqr);
     }
+    if (!it.live()) continue;
     forget(P);
     forget(Q);
     float B[K], L[K], W2[K];
