@@ -109,8 +109,11 @@ __global__ __launch_bounds__(kBoxBlock) void k_boxes_fwd(BoxesFwdArgs args) {
   }
 }
 
+// (4 waves per SIMD, as the LDS allows: left alone the 3D kernel takes 129
+// VGPRs and 3)
 template <bool Z3>
-__global__ __launch_bounds__(kBoxBlock) void k_boxes_bwd(BoxesBwdArgs args) {
+__global__ __launch_bounds__(kBoxBlock)
+__attribute__((amdgpu_waves_per_eu(4))) void k_boxes_bwd(BoxesBwdArgs args) {
   constexpr int CAP = 8;
   __shared__ float2 s_v[CAP * kBoxBlock];
   __shared__ float2 s_g[CAP * kBoxBlock];

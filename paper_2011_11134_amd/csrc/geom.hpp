@@ -80,18 +80,19 @@ __device__ __forceinline__ float fast_rcp(float v) { return __builtin_amdgcn_rcp
 // Vertex count of polygon i, clamped to [3, kmax] so that invalid counts can
 // never index outside the K register / LDS slots (their results are
 // unspecified, their memory accesses stay in bounds).
+__device__ __forceinline__ int clamp_count(int n, int kmax) { return min(max(n, 3), kmax); }
 __device__ __forceinline__ int poly_count(const uint8_t* nv, int64_t i, int kmax) {
-  const int n = nv ? (int)nv[i] : kmax;
-  return min(max(n, 3), kmax);
+  return clamp_count(nv ? (int)nv[i] : kmax, kmax);
 }
 
-// Loads polygon i of a [count][kmax][2] array into K register slots.  Slots at
-// or past n hold a copy of vertex 0, so every later computation on them stays
-// finite (their results are masked out).  FIXED callers guarantee kmax == K
-// and 16-byte aligned rows, so they always take the vector path.
+// Loads polygon i of a [count][kmax][2] array into K register slots as it
+// stands; pad_poly (once the vertex count is known) makes every later
+// computation on the slots at or past n finite (their results are masked
+// out).  FIXED callers guarantee kmax == K and 16-byte aligned rows, so they
+// always take the vector path.
 template <int K, bool FIXED>
-__device__ __forceinline__ void load_poly(const float* __restrict__ xy, int64_t i, int kmax,
-                                          bool vec4, int n, Poly<K>& p) {
+__device__ __forceinline__ void load_rows(const float* __restrict__ xy, int64_t i, int kmax,
+                                          bool vec4, Poly<K>& p) {
   const float* base = xy + i * (int64_t)kmax * 2;
   if (FIXED || vec4) {  // kmax == K, 16-byte aligned rows
 #pragma unroll
@@ -115,6 +116,11 @@ __device__ __forceinline__ void load_poly(const float* __restrict__ xy, int64_t 
       }
     }
   }
+}
+
+// Slots at or past n hold a copy of vertex 0.
+template <int K, bool FIXED>
+__device__ __forceinline__ void pad_poly(int n, Poly<K>& p) {
   if (!FIXED) {
 #pragma unroll
     for (int k = 1; k < K; ++k) {
@@ -122,6 +128,13 @@ __device__ __forceinline__ void load_poly(const float* __restrict__ xy, int64_t 
       p.y[k] = k < n ? p.y[k] : p.y[0];
     }
   }
+}
+
+template <int K, bool FIXED>
+__device__ __forceinline__ void load_poly(const float* __restrict__ xy, int64_t i, int kmax,
+                                          bool vec4, int n, Poly<K>& p) {
+  load_rows<K, FIXED>(xy, i, kmax, vec4, p);
+  pad_poly<K, FIXED>(n, p);
 }
 
 // Next vertex index after static k on a polygon of n vertices.
@@ -829,52 +842,33 @@ __device__ __forceinline__ void pair_backward(const Poly<K>& P, int n1, const Po
   const float2 X1 = rebuild_slot<K, FIXED, BLOCK>(code_at(1), n1S, nqS, s_tab, s_v, gc);
   float2 prev = X0, cur = X1, last = X0;
   float acc = 0.f;  // twice the intersection area, about X0
-  if constexpr (K == 4) {
-    // Every slot is visited (a wavefront mostly runs to its eighth slot
-    // anyway); slots at or past nx are masked by selects, not branches, so
-    // that the rolling window needs no copies: a masked slot routes a zero
-    // gradient with t = 1/den = 0 (its rebuilt point, from a padding code,
-    // may be far off or infinite and is never multiplied in).
+  // Slots are visited by the whole wavefront (all eight at K = 4: a wavefront
+  // mostly runs to its eighth anyway; at K = 8 up to its longest polygon);
+  // slots at or past nx are masked by selects, not branches, so that the
+  // rolling window needs no copies and a step's LDS reads (the next vertex's
+  // polygon slots, this one's accumulators) are in flight together: a masked
+  // slot routes a zero gradient with t = 1/den = 0 (its rebuilt point, from a
+  // padding code, may be far off or infinite and is never multiplied in).
 #pragma unroll
-    for (int r = 1; r < CAP; ++r) {
-      const bool live = r < m;
-      float2 nxt = X0;
-      SlotGeom gn = gc;
-      if (r + 1 < CAP) {
-        const float2 xr = rebuild_slot<K, FIXED, BLOCK>(code_at(r + 1), n1S, nqS, s_tab, s_v, gn);
-        const bool has = r + 1 < m;
-        nxt = has ? xr : X0;
-        const float term = (cur.x - X0.x) * (nxt.y - X0.y) - (cur.y - X0.y) * (nxt.x - X0.x);
-        acc += has ? term : 0.f;
-      }
-      // d(2I)/dX_r = (y_r+1 - y_r-1, x_r-1 - x_r+1)
-      route_slot(live ? nxt.y - prev.y : 0.f, live ? prev.x - nxt.x : 0.f, live ? gc.t : 0.f,
-                 live ? gc.idn : 0.f, gc.oa, gc.ob, gc.oc, gc.od, s_v, s_g);
-      last = live ? cur : last;
-      prev = cur;
-      cur = nxt;
-      gc = gn;
+  for (int r = 1; r < CAP; ++r) {
+    if (K == 8 && __ballot(r < m) == 0ull) break;  // uniform
+    const bool live = r < m;
+    float2 nxt = X0;
+    SlotGeom gn = gc;
+    if (r + 1 < CAP) {
+      const float2 xr = rebuild_slot<K, FIXED, BLOCK>(code_at(r + 1), n1S, nqS, s_tab, s_v, gn);
+      const bool has = r + 1 < m;
+      nxt = has ? xr : X0;
+      const float term = (cur.x - X0.x) * (nxt.y - X0.y) - (cur.y - X0.y) * (nxt.x - X0.x);
+      acc += has ? term : 0.f;
     }
-  } else {
-    // sixteen slots, of which a wavefront's polygons use far fewer: stop at
-    // the longest (branches, at the price of copies of the rolling window)
-#pragma unroll
-    for (int r = 1; r < CAP; ++r) {
-      if (r < m) {
-        float2 nxt = X0;
-        SlotGeom gn = gc;
-        if (r + 1 < CAP && r + 1 < m) {
-          nxt = rebuild_slot<K, FIXED, BLOCK>(code_at(r + 1), n1S, nqS, s_tab, s_v, gn);
-          acc += (cur.x - X0.x) * (nxt.y - X0.y) - (cur.y - X0.y) * (nxt.x - X0.x);
-        }
-        route_slot(nxt.y - prev.y, prev.x - nxt.x, gc.t, gc.idn, gc.oa, gc.ob, gc.oc, gc.od, s_v,
-                   s_g);
-        last = cur;
-        prev = cur;
-        cur = nxt;
-        gc = gn;
-      }
-    }
+    // d(2I)/dX_r = (y_r+1 - y_r-1, x_r-1 - x_r+1)
+    route_slot(live ? nxt.y - prev.y : 0.f, live ? prev.x - nxt.x : 0.f, live ? gc.t : 0.f,
+               live ? gc.idn : 0.f, gc.oa, gc.ob, gc.oc, gc.od, s_v, s_g);
+    last = live ? cur : last;
+    prev = cur;
+    cur = nxt;
+    gc = gn;
   }
   if (m > 0) route_slot(X1.y - last.y, last.x - X1.x, g0.t, g0.idn, g0.oa, g0.ob, g0.oc, g0.od,
                         s_v, s_g);

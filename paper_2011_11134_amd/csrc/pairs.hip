@@ -66,26 +66,22 @@ __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<K>()))) void k_pairs_fwd(P
   }
 }
 
+// A pair's inputs of the backward.  load<VEC>: VEC, whole rows in 16-byte loads
+// (vec4 of both polygons and flags_vec hold).
 template <int K, bool FIXED, bool Z3>
-__global__ __launch_bounds__(pairs_block<K>()) void k_pairs_bwd(PairsBwdArgs args) {
-  constexpr int BLOCK = pairs_block<K>();
-  constexpr int CAP = 2 * K;
-  __shared__ float2 s_v[CAP * BLOCK];
-  __shared__ float2 s_g[CAP * BLOCK];
-  __shared__ uint2 s_tab[256];
-  const int tid = threadIdx.x;
-  fill_code_table<K, FIXED, BLOCK>(s_tab);
-  __syncthreads();
-  const int64_t n = args.a.count;
-  for (int64_t i = (int64_t)blockIdx.x * BLOCK + tid; i < n; i += (int64_t)gridDim.x * BLOCK) {
-    const int n1 = FIXED ? K : poly_count(args.a.nv, i, args.a.kmax);
-    const int n2 = FIXED ? K : poly_count(args.b.nv, i, args.b.kmax);
-    Poly<K> P, Q;
-    load_poly<K, FIXED>(args.a.xy, i, args.a.kmax, args.a.vec4, n1, P);
-    load_poly<K, FIXED>(args.b.xy, i, args.b.kmax, args.b.vec4, n2, Q);
-    uint32_t codes[K / 2];
+struct PairIn {
+  Poly<K> P, Q;
+  int n1, n2, nx;
+  uint32_t codes[K / 2];
+  float g, lo1, hi1, lo2, hi2;
+  template <bool VEC>
+  __device__ __forceinline__ void load(const PairsBwdArgs& args, int64_t i) {
+    n1 = FIXED ? K : (args.a.nv ? (int)args.a.nv[i] : args.a.kmax);
+    n2 = FIXED ? K : (args.b.nv ? (int)args.b.nv[i] : args.b.kmax);
+    load_rows<K, VEC>(args.a.xy, i, args.a.kmax, args.a.vec4, P);
+    load_rows<K, VEC>(args.b.xy, i, args.b.kmax, args.b.vec4, Q);
     const uint8_t* row = args.xflags + i * (int64_t)args.cap;
-    if (FIXED || args.flags_vec) {
+    if (VEC || args.flags_vec) {
       if constexpr (K == 4) {
         const uint2 w = *reinterpret_cast<const uint2*>(row);
         codes[0] = w.x;
@@ -101,24 +97,65 @@ __global__ __launch_bounds__(pairs_block<K>()) void k_pairs_bwd(PairsBwdArgs arg
 #pragma unroll
       for (int w = 0; w < K / 2; ++w) codes[w] = 0xffffffffu;
 #pragma unroll
-      for (int k = 0; k < CAP; ++k) {
+      for (int k = 0; k < 2 * K; ++k) {
         if (k < args.cap) {
           const uint32_t c = row[k];
           codes[k >> 2] = (codes[k >> 2] & ~(0xffu << ((k & 3) * 8))) | (c << ((k & 3) * 8));
         }
       }
     }
-    float lo1 = 0.f, hi1 = 0.f, lo2 = 0.f, hi2 = 0.f;
+    lo1 = hi1 = lo2 = hi2 = 0.f;
     if (Z3) {
       lo1 = args.a.zlo[i];
       hi1 = args.a.zhi[i];
       lo2 = args.b.zlo[i];
       hi2 = args.b.zhi[i];
     }
+    g = args.grad[i];
+    nx = (int)args.nx[i];
+  }
+};
+
+// Held to the waves per SIMD that the LDS allows (34 KiB a workgroup: 4 at
+// K = 4, 2 at K = 8; left alone, counted 3D pairs take 131 VGPRs and 3).  At
+// K = 8 a wavefront's two per SIMD would load, compute and store in step with
+// the others, so the next pair's rows are loaded while this one is worked on,
+// and the grid is what is resident (262,144 pairs of 3..8-gons: 32.3 us before,
+// 30.3 now, with the steps' masks in place of branches).
+template <int K, bool FIXED, bool Z3>
+__global__ __launch_bounds__(pairs_block<K>())
+__attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 2))) void k_pairs_bwd(PairsBwdArgs args) {
+  constexpr int BLOCK = pairs_block<K>();
+  constexpr int CAP = 2 * K;
+  __shared__ float2 s_v[CAP * BLOCK];
+  __shared__ float2 s_g[CAP * BLOCK];
+  __shared__ uint2 s_tab[256];
+  const int tid = threadIdx.x;
+  fill_code_table<K, FIXED, BLOCK>(s_tab);
+  __syncthreads();
+  const int64_t n = args.a.count, stride = (int64_t)gridDim.x * BLOCK;
+  // (rows read in pieces are put together at once, which would wait for them)
+  const bool ahead = K == 8 && (FIXED || (args.a.vec4 && args.b.vec4 && args.flags_vec));
+  PairIn<K, FIXED, Z3> in, next;
+  int64_t i = (int64_t)blockIdx.x * BLOCK + tid;
+  if (ahead && i < n) next.template load<true>(args, i);
+  for (; i < n; i += stride) {
+    if (ahead) {
+      in = next;
+      if (i + stride < n) next.template load<true>(args, i + stride);
+    } else {
+      in.template load<FIXED>(args, i);
+    }
+    Poly<K>&P = in.P, &Q = in.Q;
+    const int n1 = FIXED ? K : clamp_count(in.n1, args.a.kmax);
+    const int n2 = FIXED ? K : clamp_count(in.n2, args.b.kmax);
+    const int nxi = in.nx;
+    pad_poly<K, FIXED>(n1, P);
+    pad_poly<K, FIXED>(n2, Q);
+    const uint32_t(&codes)[K / 2] = in.codes;
+    const float lo1 = in.lo1, hi1 = in.hi1, lo2 = in.lo2, hi2 = in.hi2, gi = in.g;
     float2 gP[K], gQ[K], gz1, gz2;
     bool thin;
-    const float gi = args.grad[i];
-    const int nxi = (int)args.nx[i];
     pair_backward<K, FIXED, Z3, BLOCK, true>(P, n1, Q, n2, gi, nxi, codes, lo1, hi1, lo2, hi2,
                                              s_v + tid, s_g + tid, s_tab, gP, gQ, gz1, gz2, thin);
     if (thin) {  // rare: the gradient again in fp64, from the polygons reloaded
@@ -158,6 +195,8 @@ __global__ __launch_bounds__(pairs_block<K>()) void k_pairs_bwd(PairsBwdArgs arg
 
 namespace {
 
+constexpr int64_t kCus = 256;  // compute units of gfx950
+
 int grid_for(int64_t n, int block, int64_t want = 0) {
   int64_t blocks = (n + block - 1) / block;
   if (want > 0 && want < blocks) blocks = want;  // persistent grid-stride launch
@@ -184,6 +223,7 @@ hipError_t fwd2(const PairsFwdArgs& a, bool z3, bool save, hipStream_t s, int64_
 template <int K, bool FIXED, bool Z3>
 hipError_t bwd3(const PairsBwdArgs& a, hipStream_t s, int64_t g) {
   constexpr int B = pairs_block<K>();
+  if (K == 8 && g == 0) g = 4 * kCus;  // resident workgroups (the LDS allows 4 a CU)
   hipLaunchKernelGGL((k_pairs_bwd<K, FIXED, Z3>), dim3(grid_for(a.a.count, B, g)), dim3(B), 0, s,
                      a);
   return hipGetLastError();
