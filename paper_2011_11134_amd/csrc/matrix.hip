@@ -876,6 +876,7 @@ struct ExactArgs {
   int64_t capacity;
   const int64_t* count;
   int cap;
+  bool flags_vec;  // cap == 2K and s_flags aligned to cap bytes: whole-row stores
   int* err;
   unsigned long long* stats;  // path statistics (NULL: off)
   // an overflowing list's tile counts are cut to its capacity here
@@ -995,9 +996,18 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_matrix_exact(ExactArgs m) {
     if (res.overflow) raise_error(m.err, kErrCapacity);
     m.s_nx[e] = (uint8_t)res.m;
     uint8_t* row = m.s_flags + e * (int64_t)m.cap;
+    if (m.flags_vec) {  // uniform: a whole row in one store
+      if constexpr (K == 4) {
+        *reinterpret_cast<uint2*>(row) = make_uint2(res.codes[0], res.codes[1]);
+      } else {
+        *reinterpret_cast<uint4*>(row) =
+            make_uint4(res.codes[0], res.codes[1], res.codes[2], res.codes[3]);
+      }
+    } else {
 #pragma unroll
-    for (int b = 0; b < CAP; ++b)
-      if (b < m.cap) row[b] = (uint8_t)(res.codes[b >> 2] >> ((b & 3) * 8));
+      for (int b = 0; b < CAP; ++b)
+        if (b < m.cap) row[b] = (uint8_t)(res.codes[b >> 2] >> ((b & 3) * 8));
+    }
     // rare: the areas again in fp64, from the polygons reloaded, and the IoU
     // written again
     if (res.thin) {
@@ -1432,6 +1442,7 @@ int matrix_forward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_t
   x.capacity = saved->capacity;
   x.count = saved->count;
   x.cap = a.kmax + b.kmax;
+  x.flags_vec = x.cap == 2 * K && aligned(saved->xflags, (uintptr_t)x.cap);
   x.err = ctx.err;
   x.stats = ctx.stats;
   x.tile_start = saved->tile_start;
