@@ -205,6 +205,39 @@ __device__ __forceinline__ void exact_signs8(uint64_t need, const float2* p_col,
   }
 }
 
+// Rows of G 16-byte pieces (64 or 128 bytes), one a lane, to memory from `out`,
+// the address of lane 0's row: through the wavefront's own columns of a
+// [..][BLOCK] float2 LDS buffer, whose 512 bytes a slot are taken as one linear
+// run, so that each store covers 1 KiB of consecutive bytes.  Stores of 16
+// bytes a lane at a stride of 64 measured 3.4 TB/s here, consecutive ones 6.1.
+// Called by a whole wavefront, once its other uses of the columns are done.
+// Piece g of row p sits at place g ^ (p / (8 / G) % G) of its row, so that
+// eight lanes reach all banks both ways.
+template <int G, int BLOCK>
+__device__ __forceinline__ void store_rows(float* out, const float4 (&v)[G],
+                                           float2* __restrict__ s_buf) {
+  static_assert(G == 4 || G == 8, "64- or 128-byte rows");
+  const uint32_t lane = threadIdx.x & 63;
+  char* base = reinterpret_cast<char*>(s_buf + (threadIdx.x & ~63u));
+  auto at = [&](uint32_t p, uint32_t g) {
+    const uint32_t b = (p * G + (g ^ (p / (8 / G) % G))) * 16u;
+    return reinterpret_cast<float4*>(base + (b >> 9) * (BLOCK * 8u) + (b & 511u));
+  };
+  wave_sync();
+#pragma unroll
+  for (int g = 0; g < G; ++g) *at(lane, g) = v[g];
+  wave_sync();
+#pragma unroll
+  for (int k = 0; k < G; ++k) {
+    const uint32_t f = k * 64 + lane;
+    *reinterpret_cast<float4*>(out + 4 * f) = *at(f / G, f % G);
+  }
+  wave_sync();
+}
+
+// Whether all of the wavefront's lanes are here.
+__device__ __forceinline__ bool whole_wave() { return __ballot(true) == ~0ull; }
+
 // Result of one pair's forward.
 template <int K>
 struct PairResult {

@@ -121,7 +121,8 @@ struct PairIn {
 // K = 8 a wavefront's two per SIMD would load, compute and store in step with
 // the others, so the next pair's rows are loaded while this one is worked on,
 // and the grid is what is resident (262,144 pairs of 3..8-gons: 32.3 us before,
-// 30.3 now, with the steps' masks in place of branches).
+// 30.3 with the steps' masks in place of branches, 28.4 with the gradient rows
+// stored in consecutive pieces).
 template <int K, bool FIXED, bool Z3>
 __global__ __launch_bounds__(pairs_block<K>())
 __attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 2))) void k_pairs_bwd(PairsBwdArgs args) {
@@ -168,24 +169,29 @@ __attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 2))) void k_pairs_bwd(PairsBwdAr
     }
     float* oa = args.ga_xy + i * (int64_t)args.a.kmax * 2;
     float* ob = args.gb_xy + i * (int64_t)args.b.kmax * 2;
-    if (FIXED || args.a.vec4) {
+    const bool whole = K == 8 && whole_wave();
+    auto store = [&](float* o, const float2(&g)[K], bool vec4, int kmax) {
+      if (FIXED || vec4) {
+        float4 v[K / 2];
 #pragma unroll
-      for (int k = 0; k < K; k += 2)
-        *reinterpret_cast<float4*>(oa + 2 * k) = make_float4(gP[k].x, gP[k].y, gP[k + 1].x, gP[k + 1].y);
-    } else {
+        for (int k = 0; k < K / 2; ++k)
+          v[k] = make_float4(g[2 * k].x, g[2 * k].y, g[2 * k + 1].x, g[2 * k + 1].y);
+        if constexpr (K == 8) {
+          if (whole) {  // uniform
+            store_rows<K / 2, BLOCK>(o - (int64_t)(tid & 63) * (2 * K), v, s_v);
+            return;
+          }
+        }
 #pragma unroll
-      for (int k = 0; k < K; ++k)
-        if (k < args.a.kmax) *reinterpret_cast<float2*>(oa + 2 * k) = gP[k];
-    }
-    if (FIXED || args.b.vec4) {
+        for (int k = 0; k < K / 2; ++k) *reinterpret_cast<float4*>(o + 4 * k) = v[k];
+      } else {
 #pragma unroll
-      for (int k = 0; k < K; k += 2)
-        *reinterpret_cast<float4*>(ob + 2 * k) = make_float4(gQ[k].x, gQ[k].y, gQ[k + 1].x, gQ[k + 1].y);
-    } else {
-#pragma unroll
-      for (int k = 0; k < K; ++k)
-        if (k < args.b.kmax) *reinterpret_cast<float2*>(ob + 2 * k) = gQ[k];
-    }
+        for (int k = 0; k < K; ++k)
+          if (k < kmax) *reinterpret_cast<float2*>(o + 2 * k) = g[k];
+      }
+    };
+    store(oa, gP, args.a.vec4, args.a.kmax);
+    store(ob, gQ, args.b.vec4, args.b.kmax);
     if (Z3) {
       *reinterpret_cast<float2*>(args.ga_z + 2 * i) = gz1;
       *reinterpret_cast<float2*>(args.gb_z + 2 * i) = gz2;

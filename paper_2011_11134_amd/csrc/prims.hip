@@ -13,7 +13,10 @@ constexpr int prim_block() {
 }
 
 // Intersection polygon of each pair: ordered vertices (absolute frame, cap
-// slots per row, 0 past nx), nx and xflags.
+// slots per row, 0 past nx), nx and xflags.  Bound by its rows: 64 or 128 bytes
+// of vertices a pair, stored in consecutive pieces (1,048,576 pairs of
+// rectangles: 36.8 us with a row a lane, 32.4 so; 262,144 of 3..8-gons: 39.5
+// and 29).
 template <int K, bool FIXED>
 __global__ __launch_bounds__(prim_block<K>())
 __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<K>()))) void k_intersect_fwd(IntersectArgs args) {
@@ -40,9 +43,19 @@ __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<K>()))) void k_intersect_f
     uint8_t* row = args.xflags + i * (int64_t)args.cap;
     float2* out = reinterpret_cast<float2*>(args.out_xy) + i * (int64_t)args.cap;
     if (FIXED || args.rows_vec) {  // cap == 2K, rows 16-byte aligned
+      if (whole_wave()) {  // uniform
+        float4 v[K];
 #pragma unroll
-      for (int k = 0; k < CAP; k += 2)
-        *reinterpret_cast<float4*>(out + k) = make_float4(ov[k].x, ov[k].y, ov[k + 1].x, ov[k + 1].y);
+        for (int k = 0; k < K; ++k)
+          v[k] = make_float4(ov[2 * k].x, ov[2 * k].y, ov[2 * k + 1].x, ov[2 * k + 1].y);
+        const int64_t lane0 = i - (int64_t)(tid & 63);
+        store_rows<K, BLOCK>(args.out_xy + lane0 * (4 * K), v, s_pt);
+      } else {
+#pragma unroll
+        for (int k = 0; k < CAP; k += 2)
+          *reinterpret_cast<float4*>(out + k) =
+              make_float4(ov[k].x, ov[k].y, ov[k + 1].x, ov[k + 1].y);
+      }
       if constexpr (K == 4) {
         *reinterpret_cast<uint2*>(row) = make_uint2(r.codes[0], r.codes[1]);
       } else {
@@ -60,7 +73,10 @@ __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<K>()))) void k_intersect_f
   }
 }
 
-// Gradient of sum <grad_xy, X> over the saved intersection vertices.
+// Gradient of sum <grad_xy, X> over the saved intersection vertices.  The rows
+// of whole polygons, counted ones too, go out in 16-byte pieces, at K = 8
+// consecutive ones (262,144 pairs of 3..8-gons: 35 us in 8-byte pieces a row a
+// lane, 22.8 so).
 template <int K, bool FIXED>
 __global__ __launch_bounds__(prim_block<K>()) void k_intersect_bwd(IntersectBwdArgs args) {
   constexpr int BLOCK = prim_block<K>();
@@ -119,12 +135,24 @@ __global__ __launch_bounds__(prim_block<K>()) void k_intersect_bwd(IntersectBwdA
                                           s_g + tid, s_tab, gP, gQ);
     float* oa = args.ga_xy + i * (int64_t)args.a.kmax * 2;
     float* ob = args.gb_xy + i * (int64_t)args.b.kmax * 2;
-    if (FIXED) {  // rows of exactly K vertices, 16-byte aligned
+    if (FIXED || args.rows_vec) {  // rows of exactly K vertices, 16-byte aligned
+      const bool whole = K == 8 && whole_wave();
+      auto store = [&](float* o, const float2(&g)[K]) {
+        float4 v[K / 2];
 #pragma unroll
-      for (int k = 0; k < K; k += 2) {
-        *reinterpret_cast<float4*>(oa + 2 * k) = make_float4(gP[k].x, gP[k].y, gP[k + 1].x, gP[k + 1].y);
-        *reinterpret_cast<float4*>(ob + 2 * k) = make_float4(gQ[k].x, gQ[k].y, gQ[k + 1].x, gQ[k + 1].y);
-      }
+        for (int k = 0; k < K / 2; ++k)
+          v[k] = make_float4(g[2 * k].x, g[2 * k].y, g[2 * k + 1].x, g[2 * k + 1].y);
+        if constexpr (K == 8) {
+          if (whole) {  // uniform
+            store_rows<K / 2, BLOCK>(o - (int64_t)(tid & 63) * (2 * K), v, s_v);
+            return;
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < K / 2; ++k) *reinterpret_cast<float4*>(o + 4 * k) = v[k];
+      };
+      store(oa, gP);
+      store(ob, gQ);
     } else {
 #pragma unroll
       for (int k = 0; k < K; ++k) {

@@ -39,8 +39,9 @@ constexpr int simple_block() {
 // bytes of LDS a lane against 160 KiB a CU, and at most 128 VGPRs, so that
 // 262,144 pairs (4,096 wavefronts) are one round.  Three waves per SIMD (192
 // bytes; 168 VGPRs and 40 bytes a lane of spills in the backward) took two
-// rounds (forward 32 us, backward 46 us there; 28.5 and 23 in one, the forward
-// 20 with the exact signs taken by whole wavefronts).
+// rounds (forward 32 us, backward 46 us there; 28.5 and 23 in one; the forward
+// 20 with the exact signs taken by whole wavefronts, the backward 19.7 with its
+// rows stored in consecutive pieces).
 template <int K>
 constexpr int simple_waves() {
   return K == 8 ? 4 : 1;
@@ -335,11 +336,12 @@ __device__ __forceinline__ float edge_cross(const Poly<K>& V, int k, int n, floa
 
 // The gradient of one polygon's vertices: each vertex moves its two edges'
 // outward normals (dy, -dx) weighted by W1 of the edge that leaves it and W2 of
-// the one that arrives, and the polygon's area by its neighbours.
+// the one that arrives, and the polygon's area by its neighbours.  s_buf: a
+// [K][BLOCK] LDS buffer whose columns the lanes are done with.
 template <int K>
 __device__ __forceinline__ void store_grad(const Poly<K>& V, int n, const float (&W1)[K],
                                            const float (&W2)[K], float cI, float cA, float* out,
-                                           int kmax, bool vec4) {
+                                           int kmax, bool vec4, float2* __restrict__ s_buf) {
   // the last edge, which arrives at vertex 0
   float wl = W2[2], lx = V.x[2], ly = V.y[2];
 #pragma unroll
@@ -365,10 +367,18 @@ __device__ __forceinline__ void store_grad(const Poly<K>& V, int n, const float 
     ppy = V.y[k];
   }
   if (vec4) {  // kmax == K, 16-byte rows
+    float4 v[K / 2];
 #pragma unroll
-    for (int k = 0; k < K; k += 2)
-      *reinterpret_cast<float4*>(out + 2 * k) =
-          make_float4(gv[k].x, gv[k].y, gv[k + 1].x, gv[k + 1].y);
+    for (int k = 0; k < K / 2; ++k)
+      v[k] = make_float4(gv[2 * k].x, gv[2 * k].y, gv[2 * k + 1].x, gv[2 * k + 1].y);
+    if constexpr (K == 8) {
+      if (whole_wave()) {  // uniform
+        store_rows<K / 2, simple_block<K>()>(out - (int64_t)(threadIdx.x & 63) * (2 * K), v, s_buf);
+        return;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < K / 2; ++k) *reinterpret_cast<float4*>(out + 4 * k) = v[k];
   } else {
 #pragma unroll
     for (int k = 0; k < K; ++k)
@@ -502,18 +512,20 @@ __attribute__((amdgpu_waves_per_eu(simple_waves<K>()))) void k_simple_bwd(Simple
       W1[k] = fmaf(0.5f, h, W1[k]);
       W2[k] = fmaf(0.5f, h, W2[k]);
     }
-    forget(P);
-    store_grad<K>(P, n1, W1, W2, cI, cA, oa, args.a.kmax, args.a.vec4);
-    // the same for Q's edges
+    // Q's edges first: the same weights from their sums, and then the columns are
+    // free for both polygons' rows
     reload_q(s, Q);
+    float V1[K], V2[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       const float2 bv = s.bm[k * BLOCK + tid];
       const float h = (float)((eq >> k) & 1u) + bv.x;
-      W1[k] = fmaf(0.5f, h, bv.y);
-      W2[k] = fmaf(0.5f, h, s.v2[k * BLOCK + tid]);
+      V1[k] = fmaf(0.5f, h, bv.y);
+      V2[k] = fmaf(0.5f, h, s.v2[k * BLOCK + tid]);
     }
-    store_grad<K>(Q, n2, W1, W2, cI, cA, ob, args.b.kmax, args.b.vec4);
+    store_grad<K>(Q, n2, V1, V2, cI, cA, ob, args.b.kmax, args.b.vec4, s.q);
+    forget(P);
+    store_grad<K>(P, n1, W1, W2, cI, cA, oa, args.a.kmax, args.a.vec4, s.q);
   }
 }
 
