@@ -1114,7 +1114,58 @@ __device__ __forceinline__ void step_row_sums(int rl, const float2 (&gv)[H], flo
   wave_sync();  // the columns are the pair kernels' staging again
 }
 
-template <int K, bool FIXED, bool Z3>
+// One step's column gradients wait in the LDS columns of their lanes: K
+// vertices, the z-extent's ends, the row of the second set and its vertex count.
+template <int K, int BLOCK>
+__device__ __forceinline__ void stage_column(float2* col, const float2 (&gq)[K], float2 gz,
+                                             int64_t row, int n) {
+#pragma unroll
+  for (int k = 0; k < K; ++k) col[k * BLOCK] = gq[k];
+  col[K * BLOCK] = gz;
+  col[(K + 1) * BLOCK] = make_float2(__int_as_float((int)row), __int_as_float((int)(row >> 32)));
+  col[(K + 2) * BLOCK].x = __int_as_float(n);
+}
+
+// Adds them to the second set's gradients; `live`: the lanes that staged one.
+// A row's floats go to consecutive lanes, so that an instruction's atomic adds
+// meet 8 (K = 8: 4) rows' cache lines and not 64: the adds leave the XCD, and
+// the lines bound the kernel where a lane added its own row's floats one by one
+// (4096 x 4096: 70 us, 38 so).  Called by all 64 lanes.
+template <int K, bool FIXED, bool Z3, int BLOCK>
+__device__ __forceinline__ void add_columns(uint64_t live, const float2* stage, float* gb_xy,
+                                            int kmax, float* gb_z) {
+  constexpr int L = 2 * K, E = 64 / L;  // floats of a row, rows an instruction takes
+  static_assert(K + 3 <= 2 * K, "a staged column fits");
+  if (live == 0) return;  // uniform
+  const int lane = (int)opaque((int64_t)(threadIdx.x & 63));  // nothing of it kept between steps
+  const float* flat = reinterpret_cast<const float*>(stage);
+  auto row_of = [&](int e) {
+    const float2 r = stage[(K + 1) * BLOCK + e];
+    return (int64_t)(((uint64_t)(uint32_t)__float_as_int(r.y) << 32) |
+                     (uint32_t)__float_as_int(r.x));
+  };
+  wave_sync();
+  for (int j = 0; j < L; ++j) {
+    const int e = j * E + lane / L, c = lane % L;
+    if ((live >> e) & 1u) {
+      const int n = FIXED ? K : __float_as_int(stage[(K + 2) * BLOCK + e].x);
+      if (c < 2 * n)
+        unsafeAtomicAdd(gb_xy + row_of(e) * (2 * kmax) + c,
+                        flat[((c >> 1) * BLOCK + e) * 2 + (c & 1)]);
+    }
+  }
+  if (Z3) {
+    for (int j = 0; j < 2; ++j) {
+      const int e = j * 32 + lane / 2, c = lane & 1;
+      if ((live >> e) & 1u)
+        unsafeAtomicAdd(gb_z + row_of(e) * 2 + c, flat[(K * BLOCK + e) * 2 + c]);
+    }
+  }
+  wave_sync();  // the columns are the pair kernels' staging again
+}
+
+// SELF: self pairs (a kernel of its own: the two roles' code together spilled).
+template <int K, bool FIXED, bool Z3, bool SELF>
 __global__ __launch_bounds__(bwd_block<K>())
 __attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 2))) void k_matrix_bwd(BwdArgs m) {
   constexpr int BLOCK = bwd_block<K>();
@@ -1177,7 +1228,8 @@ __attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 2))) void k_matrix_bwd(BwdArgs m
 #pragma unroll
     for (int j = 0; j < NACC; ++j) acc[j] = make_float2(0.f, 0.f);
     // one entry: its row in the group and the row box's gradient in gv
-    // (every slot written), or -1 (gv untouched)
+    // (every slot written), or -1 (gv untouched); of two sets also
+    // stages the column box's
     auto entry = [&](int64_t e, float2 (&gv)[H]) -> int {
       if (e < 0 || e >= e_end || e >= m.capacity) return -1;
       // the entry's saved state in one round of loads (none waits for another)
@@ -1218,7 +1270,7 @@ __attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 2))) void k_matrix_bwd(BwdArgs m
       int64_t ia = g.a0 + rg, ib = g.b0 + col;
       // self pairs: an entry below the diagonal was evaluated with the
       // column's box as P (the lower index), so the row's box is Q there
-      const bool swapped = m.seg.self_pairs && rg > col;
+      const bool swapped = SELF && rg > col;
       if (swapped) {
         const int64_t t = ia;
         ia = ib;
@@ -1233,7 +1285,7 @@ __attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 2))) void k_matrix_bwd(BwdArgs m
       // one structure, so the row's box takes its role's gradient of that
       // pair weighted by both entries' upstream gradients
       float gw = m.grad[pid];
-      if (m.seg.self_pairs) gw += m.grad[g.out0 + col * g.nb + rg];
+      if constexpr (SELF) gw += m.grad[g.out0 + col * g.nb + rg];
       float lo1 = 0.f, hi1 = 0.f, lo2 = 0.f, hi2 = 0.f;
       if (Z3) {
         lo1 = m.a.zlo[ia];
@@ -1259,25 +1311,14 @@ __attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 2))) void k_matrix_bwd(BwdArgs m
         gv[k] = own ? (swapped ? gQ[k] : gP[k]) : make_float2(0.f, 0.f);
       }
       if constexpr (Z3) gv[K] = swapped ? gz2 : gz1;
-      if (!m.seg.self_pairs) {
-        float* ob = m.gb_xy + ib * (int64_t)m.b.kmax * 2;
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-          if ((FIXED || k < n2) && k < m.b.kmax) {
-            unsafeAtomicAdd(ob + 2 * k, gQ[k].x);
-            unsafeAtomicAdd(ob + 2 * k + 1, gQ[k].y);
-          }
-        }
-        if (Z3) {
-          unsafeAtomicAdd(m.gb_z + 2 * ib, gz2.x);
-          unsafeAtomicAdd(m.gb_z + 2 * ib + 1, gz2.y);
-        }
-      }
+      if constexpr (!SELF) stage_column<K, BLOCK>(s_v + tid, gQ, gz2, ib, n2);
       return rl;
     };
     for (int64_t e0 = e_begin; e0 < e_end; e0 += 64) {  // uniform: every lane sums
       float2 gv[H];  // read only where rl >= 0
       const int rl = entry(e0 + lane, gv);
+      if constexpr (!SELF)
+        add_columns<K, FIXED, Z3, BLOCK>(__ballot(rl >= 0), stage, m.gb_xy, m.b.kmax, m.gb_z);
       step_row_sums<H, BLOCK>(rl, gv, stage, acc);
     }
     // each row of a belongs to exactly one row group: plain stores
@@ -1566,8 +1607,12 @@ int matrix_backward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_
     int64_t grid = (int64_t)ctx.cus * (shape.bwd_mult > 0 ? shape.bwd_mult : 8);
     if (!segmented) grid = std::min(grid, ceil_div(single_groups, bwd_block<KK>() / 64));
     prof_begin(ctx.prof, stream);
-    hipLaunchKernelGGL((k_matrix_bwd<KK, FX, ZZ>), dim3((unsigned)grid), dim3(bwd_block<KK>()), 0,
-                       stream, m);
+    if (self_pairs)
+      hipLaunchKernelGGL((k_matrix_bwd<KK, FX, ZZ, true>), dim3((unsigned)grid),
+                         dim3(bwd_block<KK>()), 0, stream, m);
+    else
+      hipLaunchKernelGGL((k_matrix_bwd<KK, FX, ZZ, false>), dim3((unsigned)grid),
+                         dim3(bwd_block<KK>()), 0, stream, m);
     prof_end(ctx.prof, "k_matrix_bwd", stream);
   });
   return hipGetLastError() == hipSuccess ? DGAL_OK : DGAL_EHIP;
