@@ -1032,6 +1032,7 @@ struct BwdArgs {
   SegArgs seg;
   PolyArgs a, b;
   int64_t single_groups;
+  bool split;  // one block of few row groups: a workgroup each
   const float* grad;
   const int64_t* pair_id;
   const uint8_t* s_nx;
@@ -1206,7 +1207,10 @@ __attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 2))) void k_matrix_bwd(BwdArgs m
         zero_rows(m.seg.a_off[s], m.seg.a_off[s + 1], tid, BLOCK);
   }
 
-  for (int64_t u = (int64_t)blockIdx.x * WAVES + wave; u < total; u += (int64_t)gridDim.x * WAVES) {
+  // split: the workgroup's wavefronts take the group's steps in turn
+  const int part = m.split ? wave : 0, parts = m.split ? WAVES : 1;
+  const int64_t u0 = m.split ? blockIdx.x : (int64_t)blockIdx.x * WAVES + wave;
+  for (int64_t u = u0; u < total; u += (int64_t)gridDim.x * WAVES) {
     const int s = segmented ? wave_find_segment(m.seg.group_prefix, m.seg.nseg, u) : 0;
     const int64_t tr = segmented ? u - m.seg.group_prefix[s] : u;  // row group in the segment
     const Segment g = load_segment(m.seg, s);
@@ -1314,12 +1318,27 @@ __attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 2))) void k_matrix_bwd(BwdArgs m
       if constexpr (!SELF) stage_column<K, BLOCK>(s_v + tid, gQ, gz2, ib, n2);
       return rl;
     };
-    for (int64_t e0 = e_begin; e0 < e_end; e0 += 64) {  // uniform: every lane sums
+    for (int64_t e0 = e_begin + 64 * part; e0 < e_end; e0 += 64 * parts) {  // uniform: every lane sums
       float2 gv[H];  // read only where rl >= 0
       const int rl = entry(e0 + lane, gv);
       if constexpr (!SELF)
         add_columns<K, FIXED, Z3, BLOCK>(__ballot(rl >= 0), stage, m.gb_xy, m.b.kmax, m.gb_z);
       step_row_sums<H, BLOCK>(rl, gv, stage, acc);
+    }
+    if (m.split) {  // the wavefronts' sums, in their order; one group a workgroup
+#pragma unroll
+      for (int j = 0; j < NACC; ++j) s_g[j * BLOCK + tid] = acc[j];
+      __syncthreads();
+      if (wave != 0) break;
+#pragma unroll
+      for (int w = 1; w < WAVES; ++w) {
+#pragma unroll
+        for (int j = 0; j < NACC; ++j) {
+          const float2 v = s_g[j * BLOCK + w * 64 + lane];
+          acc[j].x += v.x;
+          acc[j].y += v.y;
+        }
+      }
     }
     // each row of a belongs to exactly one row group: plain stores
 #pragma unroll
@@ -1605,7 +1624,16 @@ int matrix_backward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_
     constexpr int KK = decltype(k)::value;
     constexpr bool FX = decltype(fx)::value, ZZ = decltype(z)::value;
     int64_t grid = (int64_t)ctx.cus * (shape.bwd_mult > 0 ? shape.bwd_mult : 8);
-    if (!segmented) grid = std::min(grid, ceil_div(single_groups, bwd_block<KK>() / 64));
+    // One block of at most one round of workgroups' row groups: a workgroup a
+    // group, whose wavefronts take its steps in turn (a group of a wide block is
+    // several, one after the other in a single wavefront: 300 x 4000 34 us, 15
+    // so; 4096 x 4096 38 and 20; groups of one step, 1733 x 301: the same).
+    // More groups than that fill the chip with a wavefront each.
+    m.split = !segmented && single_groups <= (int64_t)ctx.cus * 4;
+    if (m.split)
+      grid = single_groups;
+    else if (!segmented)
+      grid = std::min(grid, ceil_div(single_groups, bwd_block<KK>() / 64));
     prof_begin(ctx.prof, stream);
     if (self_pairs)
       hipLaunchKernelGGL((k_matrix_bwd<KK, FX, ZZ, true>), dim3((unsigned)grid),
