@@ -991,8 +991,11 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_matrix_exact(ExactArgs m) {
     pair_forward<K, FIXED, kExactBlock>(P, n1, Q, n2, s_pt + tid, s_cd + tid, res, nullptr, live);
     if (!live) continue;
     count_path(m.stats, res.exact, res.thin);
-    m.iou[pid] = pair_iou<Z3>(res.inter, res.a1, res.a2, res.m, m.a.zlo, m.a.zhi, ia, m.b.zlo,
-                              m.b.zhi, ib);
+    // (the list pass wrote the zeros; a third of c5's entries are disjoint, and
+    // a scattered store costs its whole cache line)
+    const float v = pair_iou<Z3>(res.inter, res.a1, res.a2, res.m, m.a.zlo, m.a.zhi, ia, m.b.zlo,
+                                 m.b.zhi, ib);
+    if (__float_as_uint(v) != 0u) m.iou[pid] = v;
     if (res.overflow) raise_error(m.err, kErrCapacity);
     m.s_nx[e] = (uint8_t)res.m;
     uint8_t* row = m.s_flags + e * (int64_t)m.cap;
