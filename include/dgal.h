@@ -80,7 +80,8 @@ typedef struct {
 } dgal_polys;
 
 /* Creates a context on HIP device `hip_device` (allocates a small device
- * workspace).  *out is set to NULL on failure.  Returns DGAL_OK, DGAL_EINVAL
+ * workspace, and two words of pinned host memory that the kernels write
+ * deferred errors to).  *out is set to NULL on failure.  Returns DGAL_OK, DGAL_EINVAL
  * (out == NULL) or DGAL_EHIP. */
 int dgal_create(dgal_ctx **out, int hip_device);
 

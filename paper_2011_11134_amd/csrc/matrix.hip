@@ -16,7 +16,7 @@
 //     kept in the work list for the backward; and the self diagonal's 1s.
 // (k_scan_totals sums chunks of tile counts first where the table is too
 // large for each list workgroup to sum the counts before its own.)
-// c5 (64 scenes, 93.6 M pairs) takes 20 + 62 + 36 us; a kernel that tested every
+// c5 (64 scenes, 93.6 M pairs) takes 20 + 62 + 33 us; a kernel that tested every
 // pair and wrote the tiles' values (103 us), two scan passes (11), a fill of
 // the list (13) and the exact pass (31) took 162 with the segments' prefixes.
 // Grids walk the units or tiles of all segments, whose sizes are on the
@@ -26,11 +26,12 @@
 // that cover it are one contiguous range of the work list; each step's row
 // gradients are summed without atomics (sorted by row in LDS, each lane
 // adding up one (row, vertex) run in a fixed order) and every row is written
-// once.  Self pairs need
-// nothing else: entries (i, k) and (k, i) are one unordered pair evaluated with
+// once.  Self pairs need nothing else: entries (i, k) and (k, i) are one unordered pair evaluated with
 // the lower index first, so the row role of either entry is that pair's
 // gradient for the row's box, weighted by both entries' upstream gradients;
-// for two different sets the column gradients are added with global atomics.
+// for two different sets the column gradients are added with global atomics, a
+// row's floats on consecutive lanes.  A block of few row groups gives each a
+// workgroup, whose wavefronts take its steps in turn.
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
