@@ -778,7 +778,7 @@ __device__ __forceinline__ void fill_output(const ListArgs& m, int64_t b, int64_
 }
 
 // Lays out the work list: the exclusive prefix of the tile counts, and the
-// survivors' output indices from the tile state the count pass wrote (bits,
+// survivors' output indices from the tile state the cull wrote (bits,
 // origin, row length), each tile's in the order of its bits (chunk-major).  A
 // workgroup takes a contiguous range of tiles, whose start it sums from the
 // counts before it, and walks it kListTiles tiles at a time: a scan of their
