@@ -445,11 +445,16 @@ def _offsets(off):
 def _segments(n_a, n_b, a_off, b_off, self_pairs, dev, wait=True):
     """Device offsets (a_off, b_off, out_off) and total output size.  The
     three go to the device in one copy from pinned memory, on the current
-    stream (wait: and are there when this returns, for any stream)."""
+    stream (wait: and are there when this returns, for any stream).  Refused
+    under capture: a replay would copy again from memory given back by then."""
     if a_off is None:
         by = {r: ((-(-n_a // r)) * (-(-n_b // (TILE_PAIRS // r))) if n_a and n_b else 0)
               for r in TILE_ROWS_CHOICES}
         return None, None, None, 0, n_a * n_b, max(by.values()), by
+    on_gpu = dev.type == "cuda"
+    if on_gpu and torch.cuda.is_current_stream_capturing():
+        raise RuntimeError("offsets cannot be laid out under capture: build the table before it, "
+                           "with segments(), and pass it as seg")
     a_cpu = _offsets(a_off)
     b_cpu = a_cpu if (self_pairs or b_off is None) else _offsets(b_off)
     nseg = a_cpu.size - 1
@@ -463,7 +468,7 @@ def _segments(n_a, n_b, a_off, b_off, self_pairs, dev, wait=True):
     tiles = (na + _TILE_R - 1) // _TILE_R * ((nb + _TILE_C - 1) // _TILE_C)
     by = dict(zip(TILE_ROWS_CHOICES, (tiles * (sizes > 0)).sum(1).tolist()))
     two = b_cpu is not a_cpu
-    host = torch.empty((3 if two else 2) * (nseg + 1), dtype=torch.int64, pin_memory=True)
+    host = torch.empty((3 if two else 2) * (nseg + 1), dtype=torch.int64, pin_memory=on_gpu)
     h = host.numpy()
     h[:nseg + 1] = a_cpu
     if two:
@@ -505,8 +510,10 @@ def iou_matrix(a_xy, b_xy=None, a_nv=None, b_nv=None, a_z=None, b_z=None, a_off=
     pb, kb = polys(b_xy, b_nv, b_z)
     dev = a_xy.device
     if seg is None:
-        # (what follows on this stream comes after the copy of the offsets)
-        seg = _segments(a_xy.shape[0], b_xy.shape[0], a_off, b_off, self_pairs, dev, wait=False)
+        # (what follows on this stream comes after the copy of the offsets, and
+        # with check=True the table is returned after a wait for the stream)
+        seg = _segments(a_xy.shape[0], b_xy.shape[0], a_off, b_off, self_pairs, dev,
+                        wait=not check)
     d_a, d_b, d_o, nseg, total, tiles, tiles_by = seg
     iou = torch.empty(total, dtype=torch.float32, device=dev)
     given = saved

@@ -137,3 +137,28 @@ def test_segment_table_forms(dg, nseg):
     with pytest.raises(dg.DgalError) as e:
         dg.iou_matrix(xy, xy, capacity=0)
     assert e.value.status == dg.DGAL_EINVAL
+
+
+def test_host_offsets_under_capture(dg):
+    """Offsets still on the host are refused under capture (a replay would read
+    memory that has been given back), and the table may also stay on the host."""
+    rng = np.random.default_rng(3)
+    xy = dev_t(_boxes(rng, 40, 5.0))
+    off = [0, 15, 40]
+    seg = dg.segments(40, 40, off, self_pairs=True)
+    saved = dg.SavedPairs(1 << 16, 8, seg[5], xy.device)
+    want = dg.iou_matrix(xy, self_pairs=True, seg=seg)[0]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        with pytest.raises(RuntimeError):
+            dg.iou_matrix(xy, a_off=off, self_pairs=True, check=False, saved=saved)
+        with pytest.raises(RuntimeError):
+            dg.segments(40, 40, off, self_pairs=True)
+        got = dg.iou_matrix(xy, self_pairs=True, check=False, seg=seg, saved=saved)[0]
+    for _ in range(3):
+        got.zero_()
+        graph.replay()
+        assert torch.equal(got, want)
+        torch.cuda.synchronize()
+    host = dg.segments(40, 40, off, self_pairs=True, device="cpu")
+    assert [v.tolist() for v in host[:3]] == [off, off, [0, 225]]
