@@ -207,7 +207,7 @@ __device__ __forceinline__ void exact_signs8(uint64_t need, const float2* p_col,
 
 // Rows of G 16-byte pieces (64 or 128 bytes), one a lane, to memory from `out`,
 // the address of lane 0's row: through the wavefront's own columns of a
-// [..][BLOCK] float2 LDS buffer, whose 512 bytes a slot are taken as one linear
+// [..][BLOCK] float2 LDS buffer (16-byte aligned), whose 512 bytes a slot are taken as one linear
 // run, so that each store covers 1 KiB of consecutive bytes.  Stores of 16
 // bytes a lane at a stride of 64 measured 3.4 TB/s here, consecutive ones 6.1.
 // Called by a whole wavefront, once its other uses of the columns are done.

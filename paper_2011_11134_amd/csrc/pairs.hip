@@ -128,7 +128,7 @@ __global__ __launch_bounds__(pairs_block<K>())
 __attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 2))) void k_pairs_bwd(PairsBwdArgs args) {
   constexpr int BLOCK = pairs_block<K>();
   constexpr int CAP = 2 * K;
-  __shared__ float2 s_v[CAP * BLOCK];
+  __shared__ __align__(16) float2 s_v[CAP * BLOCK];
   __shared__ float2 s_g[CAP * BLOCK];
   __shared__ uint2 s_tab[256];
   const int tid = threadIdx.x;

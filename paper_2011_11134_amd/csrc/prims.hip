@@ -22,7 +22,7 @@ __global__ __launch_bounds__(prim_block<K>())
 __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<K>()))) void k_intersect_fwd(IntersectArgs args) {
   constexpr int BLOCK = prim_block<K>();
   constexpr int CAP = 2 * K;
-  __shared__ float2 s_pt[CAP * BLOCK];
+  __shared__ __align__(16) float2 s_pt[CAP * BLOCK];
   __shared__ uint16_t s_cd[CAP * BLOCK];
   const int tid = threadIdx.x;
   const int64_t n = args.a.count;
@@ -81,7 +81,7 @@ template <int K, bool FIXED>
 __global__ __launch_bounds__(prim_block<K>()) void k_intersect_bwd(IntersectBwdArgs args) {
   constexpr int BLOCK = prim_block<K>();
   constexpr int CAP = 2 * K;
-  __shared__ float2 s_v[CAP * BLOCK];
+  __shared__ __align__(16) float2 s_v[CAP * BLOCK];
   __shared__ float2 s_g[CAP * BLOCK];
   __shared__ uint2 s_tab[256];
   const int tid = threadIdx.x;

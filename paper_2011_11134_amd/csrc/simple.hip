@@ -192,7 +192,7 @@ __device__ __forceinline__ uint32_t parity8(uint32_t v) { return __builtin_popco
 // Column of Q's sums: (B', M) an edge, and with GRAD (B', V1) and V2.
 template <int K, bool GRAD, int BLOCK>
 struct SimpleLds {
-  float2 q[K * BLOCK];
+  alignas(16) float2 q[K * BLOCK];
   float2 bm[K * BLOCK];
   float v2[GRAD ? K * BLOCK : 1];
 };
