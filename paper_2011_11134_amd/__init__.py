@@ -427,7 +427,9 @@ def segments(n_a, n_b, a_off, b_off=None, self_pairs=False, device=None):
     total output size, tile capacity (the most tiles over the tile shapes),
     {tile rows: tile count}).  Build it before a HIP-graph capture and pass it as
     `seg=` (the table itself needs host-to-device copies)."""
-    dev = torch.device("cuda", torch.cuda.current_device()) if device is None else torch.device(device)
+    dev = torch.device("cuda" if device is None else device)
+    if dev.type == "cuda" and dev.index is None:
+        dev = torch.device("cuda", torch.cuda.current_device())
     return _segments(n_a, n_b, a_off, b_off, self_pairs, dev)
 
 
@@ -478,9 +480,9 @@ def _segments(n_a, n_b, a_off, b_off, self_pairs, dev, wait=True):
     o[1:] = ends
     d = host.to(dev, non_blocking=not wait)
 
-    def on_device(off, view):  # offsets given on the device are used as they are
-        there = (isinstance(off, torch.Tensor) and off.is_cuda and off.dtype == torch.int64 and
-                 off.is_contiguous() and dev.index in (None, off.device.index))
+    def on_device(off, view):  # offsets given on this device are used as they are
+        there = (isinstance(off, torch.Tensor) and on_gpu and off.device == dev and
+                 off.dtype == torch.int64 and off.is_contiguous())
         return off if there else view
 
     d_a = on_device(a_off, d[:nseg + 1])
