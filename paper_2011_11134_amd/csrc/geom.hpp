@@ -761,9 +761,11 @@ __device__ __forceinline__ const float2& at(const float2* col, uint32_t off) {
 //   A gets G - dL/de - dL/dw, B gets dL/de, C gets dL/dw - dL/df, D gets dL/df.
 // t and 1/den come from the caller (0 for a polygon vertex, whose slots are
 // all A: it adds G to A and zeros to the aliases, which are written first).
+// `live` false leaves the accumulators as they are.
 __device__ __forceinline__ void route_slot(float Gx, float Gy, float t, float idn, uint32_t oa,
                                            uint32_t ob, uint32_t oc, uint32_t od,
-                                           float2* __restrict__ s_v, float2* __restrict__ s_g) {
+                                           float2* __restrict__ s_v, float2* __restrict__ s_g,
+                                           bool live = true) {
   const float2 a = at(s_v, oa), b = at(s_v, ob), cc = at(s_v, oc), d = at(s_v, od);
   float2 ta = at(s_g, oa), tb = at(s_g, ob), tc = at(s_g, oc), td = at(s_g, od);
   const float ex = b.x - a.x, ey = b.y - a.y, fx = d.x - cc.x, fy = d.y - cc.y;
@@ -782,10 +784,12 @@ __device__ __forceinline__ void route_slot(float Gx, float Gy, float t, float id
   td.y += gfy;
   ta.x += Gx - gex - gwx;
   ta.y += Gy - gey - gwy;
-  at(s_g, ob) = tb;
-  at(s_g, oc) = tc;
-  at(s_g, od) = td;
-  at(s_g, oa) = ta;
+  if (live) {
+    at(s_g, ob) = tb;
+    at(s_g, oc) = tc;
+    at(s_g, od) = td;
+    at(s_g, oa) = ta;
+  }
 }
 
 // t and 1/den of the vertex in slots (oa, ob, oc, od); its position is
@@ -881,7 +885,10 @@ __device__ __forceinline__ void pair_backward(const Poly<K>& P, int n1, const Po
   // rolling window needs no copies and a step's LDS reads (the next vertex's
   // polygon slots, this one's accumulators) are in flight together: a masked
   // slot routes a zero gradient with t = 1/den = 0 (its rebuilt point, from a
-  // padding code, may be far off or infinite and is never multiplied in).
+  // padding code, may be far off or infinite and is never multiplied in).  At
+  // K = 8, where how many slots a lane visits depends on the wavefront's other
+  // pairs, a masked slot is not stored either: next to an infinite or NaN
+  // vertex its zeros would be NaN.
 #pragma unroll
   for (int r = 1; r < CAP; ++r) {
     if (K == 8 && __ballot(r < m) == 0ull) break;  // uniform
@@ -897,7 +904,7 @@ __device__ __forceinline__ void pair_backward(const Poly<K>& P, int n1, const Po
     }
     // d(2I)/dX_r = (y_r+1 - y_r-1, x_r-1 - x_r+1)
     route_slot(live ? nxt.y - prev.y : 0.f, live ? prev.x - nxt.x : 0.f, live ? gc.t : 0.f,
-               live ? gc.idn : 0.f, gc.oa, gc.ob, gc.oc, gc.od, s_v, s_g);
+               live ? gc.idn : 0.f, gc.oa, gc.ob, gc.oc, gc.od, s_v, s_g, K == 4 || live);
     last = live ? cur : last;
     prev = cur;
     cur = nxt;
