@@ -918,18 +918,25 @@ __device__ __forceinline__ bool locate(const SegArgs& sa, int64_t pid, SegCache&
 }
 
 // The 1s on the diagonals of self blocks, a row a thread, by the last
-// workgroups of the exact pass (the ones that most often have no entries).
+// workgroups of the exact pass (the ones that most often have no entries).  The
+// rows are found by their row groups, which only the accepted segments own: a
+// rejected one's offsets need not be in order, so a row's place in a_off does
+// not tell its segment.
 __device__ __forceinline__ void write_diagonals(const SegArgs& a, float* iou) {
+  const bool segmented = a.a_off != nullptr;
+  const int64_t groups = segmented ? a.group_prefix[a.nseg]
+                                   : (a.a_count + kGroupRows - 1) / kGroupRows;
   const int64_t threads = (int64_t)gridDim.x * kExactBlock;
-  for (int64_t r0 = ((int64_t)gridDim.x - 1 - blockIdx.x) * kExactBlock + (threadIdx.x & ~63);
-       r0 < a.a_count; r0 += threads) {  // the wavefront's 64 rows
-    const int64_t row = r0 + (threadIdx.x & 63);
-    const bool segmented = a.a_off != nullptr;
-    const int s0 = segmented ? wave_find_segment(a.a_off, a.nseg, wave_first(r0)) : 0;
-    Segment g = load_segment(a, s0);
-    if (segmented && row >= g.a0 + g.na) g = load_segment(a, find_segment(a.a_off, a.nseg, row));
-    const int64_t r = row - g.a0;
-    if (g.ok && r >= 0 && r < g.na) iou[g.out0 + r * (g.nb + 1)] = 1.f;
+  for (int64_t t0 = ((int64_t)gridDim.x - 1 - blockIdx.x) * kExactBlock + (threadIdx.x & ~63);
+       t0 < groups * kGroupRows; t0 += threads) {  // the wavefront's 64 rows
+    const int64_t u = (t0 + (threadIdx.x & 63)) / kGroupRows;
+    int s = segmented ? wave_find_segment(a.group_prefix, a.nseg, wave_first(t0 / kGroupRows)) : 0;
+    if (u >= groups) continue;
+    if (segmented && u >= a.group_prefix[s + 1]) s = find_segment(a.group_prefix, a.nseg, u);
+    const Segment g = load_segment(a, s);
+    const int64_t r = (u - (segmented ? a.group_prefix[s] : 0)) * kGroupRows +
+                      (threadIdx.x & (kGroupRows - 1));
+    if (g.ok && r < g.na) iou[g.out0 + r * (g.nb + 1)] = 1.f;
   }
 }
 
