@@ -395,9 +395,10 @@ int dgal_path_stats(dgal_ctx *ctx, int64_t *pairs, int64_t *fp64_pairs, int64_t 
 
 /* Launch-shape autotuning of the batched kernels: the grid of the pair
  * kernels; for the matrix forward, the tile shape (4, 8 or 16 rows, unless
- * saved->tile_rows fixes it) and the persistent grids of its count and exact
+ * saved->tile_rows fixes it) and the persistent grids of its cull and exact
  * passes; the persistent grid of the matrix backward (Sec. II-C: kernels
- * specialised per size).  Kinds of call are told apart by entry point, vertex
+ * specialised per size; a single block whose grid is its row groups has
+ * nothing to choose).  Kinds of call are told apart by entry point, vertex
  * capacity 4 or 8, fixed-size or counted polygons, 2D or 3D, one block or
  * segments, and a size bucket (the bit lengths of the counts).  A call of a
  * kind with no choice yet takes the process-wide store's (see
@@ -422,8 +423,10 @@ int dgal_set_autotune(dgal_ctx *ctx, int32_t enable);
 int dgal_autotune_report(dgal_ctx *ctx, char *buf, int64_t size);
 
 /* The process-wide store of tuned launch shapes, shared by every context and
- * keyed by "<gfx arch>/<kind>/K<4|8>/fixed<0|1>/z<0|1>/seg<0|1>/b<bucket>",
- * and its JSON file:
+ * keyed by "<gfx arch>/<kind>.<revision>/K<4|8>/fixed<0|1>/z<0|1>/seg<0|1>/
+ * b<bucket>" (the revision of the kind's kernels: a choice made for another
+ * one loads, and is kept in the file, but no call takes it), and its JSON
+ * file:
  *   {"format": "dgal-tune-cache", "version": 1, "entries": [{"key": "...",
  *    "grid": G, "cull_mult": C, "exact_mult": E, "bwd_mult": B,
  *    "tile_rows": R, "ms": T}, ...]}

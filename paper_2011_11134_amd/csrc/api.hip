@@ -14,12 +14,15 @@
 // A kind of call the autotuner tells apart: the entry point, register
 // capacity K, fixed size, 3D, segmented (or saving, for the pair forward) and
 // a size bucket (bit lengths of the counts).  Its text form, prefixed with
-// the GPU architecture, keys the process-wide store and the cache file.
+// the GPU architecture, keys the process-wide store and the cache file.  The
+// number after a kind is raised whenever its kernels, or what a shape means to
+// them, change: a choice measured on others is then not found again.
 struct TuneKey {
   int kind, K, fixed, z3, seg;
   std::string bucket;
   std::string text(const std::string& arch) const {
-    static const char* names[] = {"pairs_fwd", "pairs_bwd", "matrix_fwd", "matrix_bwd"};
+    static const char* names[] = {"pairs_fwd.2", "pairs_bwd.2", "matrix_fwd.2",
+                                  "matrix_bwd.2"};
     char b[160];
     snprintf(b, sizeof(b), "%s/%s/K%d/fixed%d/z%d/seg%d/b%s", arch.c_str(), names[kind], K, fixed,
              z3, seg, bucket.c_str());
@@ -204,15 +207,15 @@ std::vector<dgal::LaunchShape> pair_grids(int cus) {
   return v;
 }
 
-// Tile rows (unless the caller fixed them) x persistent grids of the count
+// Tile rows (unless the caller fixed them) x persistent grids of the cull
 // and exact passes.  16-row tiles are tried only when the caller fixed them:
 // the backward's 8-row groups scan each 16-row tile row's entries twice (c5
 // backward 71 -> 85 us), a cost the forward's timing cannot see.
 std::vector<dgal::LaunchShape> matrix_fwd_shapes(int fixed_rows) {
   std::vector<dgal::LaunchShape> v;
-  for (int r : {8, 4, 16}) {  // the built-in shape (8, 32, 8) first
+  for (int r : {8, 4, 16}) {  // the built-in shape (8, 8, 8) first
     if (fixed_rows != 0 ? r != fixed_rows : r == 16) continue;
-    for (int c : {32, 16, 64})
+    for (int c : {8, 4, 16})
       for (int e : {8, 4, 16}) {
         dgal::LaunchShape s;
         s.tile_rows = r;
@@ -474,12 +477,15 @@ int dgal_iou_backward(dgal_ctx* ctx, int32_t mode, dgal_polys a, dgal_polys b,
   }
   if (mode == DGAL_MATRIX) {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    auto key = [&] { return matrix_key(kTuneMatrixBwd, a, b, a_off, nseg); };
-    return run_tuned(ctx, key, matrix_bwd_shapes, s, [&](const dgal::LaunchShape& sh) {
+    auto launch = [&](const dgal::LaunchShape& sh) {
       return dgal::matrix_backward(ctx->v, a, b, a_off, b_off, out_off, nseg, self_pairs,
                                    grad_iou, out_size, saved, grad_a_xy, grad_b_xy, grad_a_z,
                                    grad_b_z, s, sh);
-    });
+    };
+    // a block whose grid is its row groups has one shape: nothing to choose
+    if (dgal::matrix_bwd_split(ctx->v, a_off != nullptr, a.count)) return launch(dgal::LaunchShape());
+    auto key = [&] { return matrix_key(kTuneMatrixBwd, a, b, a_off, nseg); };
+    return run_tuned(ctx, key, matrix_bwd_shapes, s, launch);
   }
   return DGAL_EINVAL;
 }

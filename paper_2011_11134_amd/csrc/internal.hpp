@@ -224,6 +224,19 @@ int matrix_backward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_
                     float* grad_a_xy, float* grad_b_xy, float* grad_a_z, float* grad_b_z,
                     hipStream_t stream, const LaunchShape& shape = LaunchShape());
 
+constexpr int kGroupRows = 8;  // rows of a row group of the matrix backward
+
+// Whether the matrix backward gives each row group a workgroup (its grid is then
+// the row groups, whatever the launch shape).
+// One block of at most one round of workgroups' row groups: a workgroup a
+// group, whose wavefronts take its steps in turn (a group of a wide block is
+// several, one after the other in a single wavefront: 300 x 4000 34 us, 15
+// so; 4096 x 4096 38 and 20; groups of one step, 1733 x 301: the same).
+// More groups than that fill the chip with a wavefront each.
+inline bool matrix_bwd_split(const CtxView& ctx, bool segmented, int64_t rows) {
+  return !segmented && (rows + kGroupRows - 1) / kGroupRows <= (int64_t)ctx.cus * 4;
+}
+
 // The allocation-free forward: dgal_iou_matrix with its work list, tile state
 // and workspace in the library's static device scratch (matrix.hip).
 // matrix_scratch_init takes the scratch's device address once per device

@@ -43,7 +43,6 @@
 namespace dgal {
 
 constexpr int kTilePairs = DGAL_TILE_PAIRS;
-constexpr int kGroupRows = 8;     // rows of a backward row group
 constexpr int kCullBlock = 256;   // four independent wavefronts
 constexpr int kScanBlock = 1024;
 constexpr int kListBlock = 256;
@@ -1481,7 +1480,7 @@ int matrix_forward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_t
   c.err = ctx.err;
   // the units' workgroups; with segments, whose sizes are on the device, they
   // walk the units in grid strides
-  int64_t cull_grid = (int64_t)ctx.cus * (shape.cull_mult > 0 ? shape.cull_mult : 32) / 4;
+  int64_t cull_grid = (int64_t)ctx.cus * (shape.cull_mult > 0 ? shape.cull_mult : 8);
   if (segmented) {
     c.single_units = 0;
     cull_grid = std::max<int64_t>(1, std::min(cull_grid, saved->tile_capacity));
@@ -1635,12 +1634,7 @@ int matrix_backward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_
     constexpr int KK = decltype(k)::value;
     constexpr bool FX = decltype(fx)::value, ZZ = decltype(z)::value;
     int64_t grid = (int64_t)ctx.cus * (shape.bwd_mult > 0 ? shape.bwd_mult : 8);
-    // One block of at most one round of workgroups' row groups: a workgroup a
-    // group, whose wavefronts take its steps in turn (a group of a wide block is
-    // several, one after the other in a single wavefront: 300 x 4000 34 us, 15
-    // so; 4096 x 4096 38 and 20; groups of one step, 1733 x 301: the same).
-    // More groups than that fill the chip with a wavefront each.
-    m.split = !segmented && single_groups <= (int64_t)ctx.cus * 4;
+    m.split = matrix_bwd_split(ctx, segmented, a.count);
     if (m.split)
       grid = single_groups;
     else if (!segmented)

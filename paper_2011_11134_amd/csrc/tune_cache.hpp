@@ -10,7 +10,8 @@ namespace dgal {
 
 // Launch shape of one call, chosen by the autotuner (0 = built-in default).
 // grid: workgroups of a grid-stride elementwise kernel (0 => one lane per
-// item); the matrix multipliers scale the persistent grids by the CU count;
+// item, or the kernel's own resident grid); the matrix multipliers are the
+// persistent grids' workgroups per CU;
 // tile_rows sets the matrix tiles (tile_rows x 2048 / tile_rows pairs).
 struct LaunchShape {
   int64_t grid = 0;
@@ -28,7 +29,7 @@ bool shape_valid(const LaunchShape& s);
 
 // The store: key -> (shape, milliseconds of the timed runs that chose it).
 // Keys name the GPU architecture and the kind of call, e.g.
-// "gfx950/matrix_fwd/K4/fixed1/z1/seg1/b13.6".  Thread-safe.
+// "gfx950/matrix_fwd.2/K4/fixed1/z1/seg1/b13.6".  Thread-safe.
 bool tune_store_get(const std::string& key, LaunchShape* out);
 void tune_store_put(const std::string& key, const LaunchShape& s, double ms);
 void tune_store_clear();
