@@ -207,6 +207,25 @@ std::vector<dgal::LaunchShape> pair_grids(int cus) {
   return v;
 }
 
+// The 8-slot pair backward's grid is what is resident unless a shape says
+// otherwise (the LDS allows 4 workgroups a CU), also for the rows that are not
+// loaded ahead: 262,144 pairs of 5-gons take 27.6 us with a workgroup for every
+// block of pairs and 25.8 so, 3..7-gons 37.8 and 33.8, unaligned rows 38.1 and
+// 34.8.
+int64_t pairs_bwd_grid(int K, int cus, int64_t grid) {
+  return K == 8 && grid == 0 ? (int64_t)cus * 4 : grid;
+}
+
+// Its candidates: those grids, with a workgroup for every block of pairs (the
+// largest grid: the launch needs no more) where the default is the resident one.
+std::vector<dgal::LaunchShape> pair_bwd_grids(int K, int cus) {
+  std::vector<dgal::LaunchShape> v = pair_grids(cus);
+  if (K == 8)
+    for (dgal::LaunchShape& s : v)
+      if (s.grid == (int64_t)cus * 4) s.grid = dgal::kMaxGrid;
+  return v;
+}
+
 // Tile rows (unless the caller fixed them) x persistent grids of the cull
 // and exact passes.  16-row tiles are tried only when the caller fixed them:
 // the backward's 8-row groups scan each 16-row tile row's entries twice (c5
@@ -467,8 +486,9 @@ int dgal_iou_backward(dgal_ctx* ctx, int32_t mode, dgal_polys a, dgal_polys b,
                        args.a.vec4 && args.b.vec4 && args.flags_vec;
     hipStream_t s = static_cast<hipStream_t>(stream);
     auto key = [&] { return TuneKey{kTunePairsBwd, K, fixed, z3, 0, bucket_of(a.count)}; };
-    return run_tuned(ctx, key, [&] { return pair_grids(ctx->v.cus); }, s,
-                     [&](const dgal::LaunchShape& sh) {
+    return run_tuned(ctx, key, [&] { return pair_bwd_grids(K, ctx->v.cus); }, s,
+                     [&](dgal::LaunchShape sh) {
+                       sh.grid = pairs_bwd_grid(K, ctx->v.cus, sh.grid);
                        dgal::prof_begin(ctx->v.prof, s);
                        const hipError_t e = dgal::launch_pairs_bwd(args, K, fixed, z3, s, sh);
                        dgal::prof_end(ctx->v.prof, "k_pairs_bwd", s);

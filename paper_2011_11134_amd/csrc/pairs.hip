@@ -201,8 +201,6 @@ __attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 2))) void k_pairs_bwd(PairsBwdAr
 
 namespace {
 
-constexpr int64_t kCus = 256;  // compute units of gfx950
-
 int grid_for(int64_t n, int block, int64_t want = 0) {
   int64_t blocks = (n + block - 1) / block;
   if (want > 0 && want < blocks) blocks = want;  // persistent grid-stride launch
@@ -229,7 +227,6 @@ hipError_t fwd2(const PairsFwdArgs& a, bool z3, bool save, hipStream_t s, int64_
 template <int K, bool FIXED, bool Z3>
 hipError_t bwd3(const PairsBwdArgs& a, hipStream_t s, int64_t g) {
   constexpr int B = pairs_block<K>();
-  if (K == 8 && g == 0) g = 4 * kCus;  // resident workgroups (the LDS allows 4 a CU)
   hipLaunchKernelGGL((k_pairs_bwd<K, FIXED, Z3>), dim3(grid_for(a.a.count, B, g)), dim3(B), 0, s,
                      a);
   return hipGetLastError();

@@ -220,7 +220,7 @@ bool key_valid(const std::string& k) {
 }  // namespace
 
 bool shape_valid(const LaunchShape& s) {
-  return s.grid >= 0 && s.grid <= (1 << 24) && s.cull_mult >= 0 && s.cull_mult <= 64 &&
+  return s.grid >= 0 && s.grid <= kMaxGrid && s.cull_mult >= 0 && s.cull_mult <= 64 &&
          s.exact_mult >= 0 && s.exact_mult <= 64 && s.bwd_mult >= 0 && s.bwd_mult <= 64 &&
          (s.tile_rows == 0 || s.tile_rows == 4 || s.tile_rows == 8 || s.tile_rows == 16);
 }
@@ -290,7 +290,7 @@ int tune_store_load(const char* path) {
     const JVal* key = e.get("key");
     if (key == nullptr || key->type != JVal::kStr || !key_valid(key->str)) return DGAL_EINVAL;
     int64_t grid, cull, exact, bwd, rows;
-    if (!int_field(e, "grid", 0, 1 << 24, &grid) || !int_field(e, "cull_mult", 0, 64, &cull) ||
+    if (!int_field(e, "grid", 0, kMaxGrid, &grid) || !int_field(e, "cull_mult", 0, 64, &cull) ||
         !int_field(e, "exact_mult", 0, 64, &exact) || !int_field(e, "bwd_mult", 0, 64, &bwd) ||
         !int_field(e, "tile_rows", 0, 16, &rows))
       return DGAL_EINVAL;

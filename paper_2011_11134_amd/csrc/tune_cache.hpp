@@ -24,6 +24,8 @@ inline bool operator==(const LaunchShape& x, const LaunchShape& y) {
          x.bwd_mult == y.bwd_mult && x.tile_rows == y.tile_rows;
 }
 
+constexpr int64_t kMaxGrid = 1 << 24;  // largest LaunchShape::grid
+
 // Whether every field is one the library can launch (the file is input).
 bool shape_valid(const LaunchShape& s);
 
