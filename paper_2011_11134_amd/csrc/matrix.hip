@@ -275,6 +275,7 @@ __device__ __forceinline__ void divmod(int64_t v, int64_t d, int64_t& q, int64_t
 // a segment.  The output's initial values are written by the list pass.
 constexpr int kUnitRows = kCullBlock;  // 64 rows a wavefront
 constexpr int kBins = 32;              // bins per axis of the masks' broad phase
+constexpr int kSparse = 16;            // most candidates of a word tested one by one
 constexpr int kFillStep = 4 * kCullBlock;  // values a fill workgroup stores at once
 
 // The pass's work in one segment (none where the segment is rejected).
@@ -457,6 +458,7 @@ struct MaskLds {
   // end lies in bin b or below, entry kBins + b those whose upper end lies
   // in bin kBins - 1 - b or above
   uint64_t bm[Z3 ? 3 : 2][C / 64][2 * kBins];
+  float2 bins[Z3 ? 3 : 2][C / 64];      // their first coordinate, and bins per unit length
 };
 
 // Masks of one unit: kUnitRows rows from row r0 of segment g against the
@@ -466,16 +468,30 @@ struct MaskLds {
 // bits of its four (six) bound differences are all clear.  Only the pairs
 // whose bins overlap on every axis are tested: the columns' bins are kept as
 // bit sets, so that the two (three) axes cost a lane four (six) LDS reads for
-// 64 columns, and on c5 leave about one pair of them to test.  Bound by
+// 64 columns, and on c5 leave about one pair of them to test.  A word's bins
+// span the bounds of its own 64 columns: boxes laid out in an order have bins
+// where they lie, and a far box costs one word its bins, not the tile.  A word
+// that leaves a lane more than kSparse candidates (a far box, a crowd) is tested
+// whole, every lane the same column, whose bounds are one LDS broadcast: no
+// layout costs more than a test of every pair (a candidate alone takes some 200
+// cycles of latency, two at a time; a column of all 7 to 10 vector
+// instructions; kSparse 8 took 3% more on a 3D crowd, 24 the same).  Bound by
 // latency (the LDS reads of the tests; the busiest lane has about four): 20 us
-// on c5, where testing every pair, 10 vector instructions for 64 pairs, took
-// 70 us without its stores; 5.5 us on 4096 x 4096.  Rows and columns
-// past the block, and empty z extents, survive nothing.
+// on c5, 7.5 on 4096 x 4096.  Forwards of other layouts, in us: kernels that
+// tested every pair and wrote the zeros / bins of the tile's first 64 columns
+// for all of it / so:
+//   4096 x 4096    random 39 / 30.5 / 30.5, sorted along x 38 / 34 / 32.5, in
+//                  grid order 39 / 44 / 33, a far box every 256 39 / 35 / 31,
+//                  every 64 38 / 57 / 34, a crowd (10% overlap) 80 / 72 / 70
+//   64 3D scenes   random 156 / 114 / 114, sorted 149 / 116 / 113, far boxes
+//                  160 / 128 / 118 and 157 / 185 / 140, a crowd 357 / 302 / 302
+// Rows and columns past the block, and empty z extents, survive nothing.
 template <int K, bool FIXED, bool Z3, int R>
 __device__ __forceinline__ void mask_unit(const CullArgs& m, const Segment& g, int64_t tile0,
                                           int64_t r0, int64_t tc,
                                           MaskLds<Z3, kTilePairs / R>& s) {
   constexpr int C = kTilePairs / R, W = C / 64, D = Z3 ? 3 : 2, WAVES = kCullBlock / 64;
+  constexpr int kUnroll = Z3 ? 4 : 8;
   constexpr int RL = R == 4 ? 2 : (R == 8 ? 3 : 4);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -496,21 +512,6 @@ __device__ __forceinline__ void mask_unit(const CullArgs& m, const Segment& g, i
   }
   for (int i = tid; i < D * W * 2 * kBins; i += kCullBlock) (&s.bm[0][0][0])[i] = 0ull;
   __syncthreads();
-  // the bins span the first 64 columns' bounds (others are clamped to them)
-  float lo[D], scale[D];
-  {
-    const bool in = lane < nc && !(Z3 && s.z[Z3 ? lane : 0].x == __builtin_inff());
-    const float4 b = s.xy[lane];
-    float2 z = make_float2(0.f, 0.f);
-    if constexpr (Z3) z = s.z[lane];
-    const float l[3] = {b.x, b.y, z.x}, h[3] = {b.z, b.w, z.y};
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      lo[a] = wave_min(in ? l[a] : __builtin_inff());
-      const float hi = -wave_min(in ? -h[a] : __builtin_inff());
-      scale[a] = (float)kBins * fast_rcp(hi - lo[a]);
-    }
-  }
   for (int w = wave; w < W; w += WAVES) {  // each wavefront its own words
     const int c = w * 64 + lane;
     const float4 b = s.xy[c];
@@ -519,12 +520,16 @@ __device__ __forceinline__ void mask_unit(const CullArgs& m, const Segment& g, i
     const bool in = c < nc && !(Z3 && z.x == __builtin_inff());
     const float l[3] = {b.x, b.y, z.x}, h[3] = {b.z, b.w, z.y};
     const uint64_t bit = 1ull << lane;
-    if (in) {
 #pragma unroll
-      for (int a = 0; a < D; ++a) {
-        __hip_atomic_fetch_or(&s.bm[a][w][bin_of(l[a], lo[a], scale[a])], bit, __ATOMIC_RELAXED,
+    for (int a = 0; a < D; ++a) {  // the bins span these 64 columns' bounds
+      const float lo = wave_min(in ? l[a] : __builtin_inff());
+      const float hi = -wave_min(in ? -h[a] : __builtin_inff());
+      const float scale = (float)kBins * fast_rcp(hi - lo);
+      if (lane == 0) s.bins[a][w] = make_float2(lo, scale);
+      if (in) {
+        __hip_atomic_fetch_or(&s.bm[a][w][bin_of(l[a], lo, scale)], bit, __ATOMIC_RELAXED,
                               __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_fetch_or(&s.bm[a][w][2 * kBins - 1 - bin_of(h[a], lo[a], scale[a])], bit,
+        __hip_atomic_fetch_or(&s.bm[a][w][2 * kBins - 1 - bin_of(h[a], lo, scale)], bit,
                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
@@ -544,17 +549,7 @@ __device__ __forceinline__ void mask_unit(const CullArgs& m, const Segment& g, i
   if (row < g.na) rb = box_bounds<K, FIXED, Z3>(m.a, g.a0 + row);
   const bool live = row < g.na && !(Z3 && !(rb.hi > rb.lo));
   if (Z3) rb.hi = below(rb.hi);
-  // bit-set entries: columns that begin at or below the row's end, and end
-  // at or above its start
-  int e0[D], e1[D];
-  {
-    const float l[3] = {rb.x0, rb.y0, rb.lo}, h[3] = {rb.x1, rb.y1, rb.hi};
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      e0[a] = bin_of(h[a], lo[a], scale[a]);
-      e1[a] = 2 * kBins - 1 - bin_of(l[a], lo[a], scale[a]);
-    }
-  }
+  const float rl[3] = {rb.x0, rb.y0, rb.lo}, rh[3] = {rb.x1, rb.y1, rb.hi};
   const int64_t tr = row >> RL;
   const int64_t u = tile0 + tr * col_tiles_of(g, RL) + tc;
   const bool have = row < (tile_rows_of(g, RL) << RL) && u < m.tile_capacity;
@@ -565,15 +560,19 @@ __device__ __forceinline__ void mask_unit(const CullArgs& m, const Segment& g, i
     uint64_t keep = 0ull;
     if (w * 64 < nc) {  // uniform
       uint64_t cand = live ? ~0ull : 0ull;
+      // columns that begin at or below the row's end, and end at or above its start
 #pragma unroll
-      for (int a = 0; a < D; ++a) cand &= s.bm[a][w][e0[a]] & s.bm[a][w][e1[a]];
+      for (int a = 0; a < D; ++a) {
+        const float2 b = s.bins[a][w];
+        cand &= s.bm[a][w][bin_of(rh[a], b.x, b.y)] &
+                s.bm[a][w][2 * kBins - 1 - bin_of(rl[a], b.x, b.y)];
+      }
       if (m.seg.self_pairs) {  // the diagonal
         const int64_t dd = row - (cb + w * 64);
         if (dd >= 0 && dd < 64) cand &= ~(1ull << dd);
       }
-      while (cand != 0ull) {
-        const int j = w * 64 + __builtin_ctzll(cand);
-        const uint64_t rest = cand & (cand - 1ull);
+      // sign bit clear: column j and the row overlap
+      auto gaps = [&](int j) {
         const float4 b = s.xy[j];
         uint32_t bits = gap_bits(rb.x1, b.x) | gap_bits(b.z, rb.x0) | gap_bits(rb.y1, b.y) |
                         gap_bits(b.w, rb.y0);
@@ -581,8 +580,26 @@ __device__ __forceinline__ void mask_unit(const CullArgs& m, const Segment& g, i
           const float2 z = s.z[j];
           bits |= gap_bits(rb.hi, z.x) | gap_bits(z.y, rb.lo);
         }
-        if ((int32_t)bits >= 0) keep |= cand ^ rest;
-        cand = rest;
+        return bits;
+      };
+      if (__ballot(__popcll(cand) > kSparse) == 0ull) {  // uniform
+        while (cand != 0ull) {  // the first and the last one left
+          const int j = __builtin_ctzll(cand), k = 63 - __builtin_clzll(cand);
+          const uint64_t bj = 1ull << j, bk = 1ull << k;
+          const uint32_t gj = gaps(w * 64 + j), gk = gaps(w * 64 + k);
+          if ((int32_t)gj >= 0) keep |= bj;
+          if ((int32_t)gk >= 0) keep |= bk;
+          cand &= ~(bj | bk);
+        }
+      } else {  // every column, the same in all lanes
+        uint32_t half[2] = {0u, 0u};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll kUnroll
+          for (int j = 31; j >= 0; --j)
+            half[h] = __builtin_amdgcn_alignbit(half[h], gaps(w * 64 + h * 32 + j), 31);
+        }
+        keep = cand & ~((uint64_t)half[1] << 32 | half[0]);
       }
     }
     n += (uint32_t)__popcll(keep);
@@ -603,7 +620,8 @@ __device__ __forceinline__ void mask_unit(const CullArgs& m, const Segment& g, i
 }
 
 template <int K, bool FIXED, bool Z3, int R>
-__global__ __launch_bounds__(kCullBlock) void k_matrix_cull(CullArgs m) {
+__global__ __launch_bounds__(kCullBlock)
+__attribute__((amdgpu_waves_per_eu(R == 4 || !Z3 ? 5 : 7))) void k_matrix_cull(CullArgs m) {
   static_assert(R == 4 || R == 8 || R == 16, "tile rows");
   constexpr int C = kTilePairs / R;
   constexpr int RL = R == 4 ? 2 : (R == 8 ? 3 : 4);
