@@ -16,10 +16,14 @@ constexpr int prim_block() {
 // slots per row, 0 past nx), nx and xflags.  Bound by its rows: 64 or 128 bytes
 // of vertices a pair, stored in consecutive pieces (1,048,576 pairs of
 // rectangles: 36.8 us with a row a lane, 32.4 so; 262,144 of 3..8-gons: 39.5
-// and 29).
-template <int K, bool FIXED>
+// and 29).  ROWS: cap == 2K and every row 16-byte aligned; the other rows have
+// an instance of their own, and both are held to the 4 waves per SIMD that make
+// 262,144 pairs at K = 4 one round: with both forms in one kernel left alone,
+// triangles took 16.3 us (137 VGPRs, 3 waves) and take 12.4 now, a million
+// pairs of 3..7-gons 127 (52 bytes a lane spilled) and 120.5.
+template <int K, bool FIXED, bool ROWS>
 __global__ __launch_bounds__(prim_block<K>())
-__attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<K>()))) void k_intersect_fwd(IntersectArgs args) {
+__attribute__((amdgpu_waves_per_eu(4))) void k_intersect_fwd(IntersectArgs args) {
   constexpr int BLOCK = prim_block<K>();
   constexpr int CAP = 2 * K;
   __shared__ __align__(16) float2 s_pt[CAP * BLOCK];
@@ -42,7 +46,7 @@ __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<K>()))) void k_intersect_f
     args.nx[i] = (uint8_t)r.m;
     uint8_t* row = args.xflags + i * (int64_t)args.cap;
     float2* out = reinterpret_cast<float2*>(args.out_xy) + i * (int64_t)args.cap;
-    if (FIXED || args.rows_vec) {  // cap == 2K, rows 16-byte aligned
+    if constexpr (ROWS) {  // cap == 2K, rows 16-byte aligned
       if (whole_wave()) {  // uniform
         float4 v[K];
 #pragma unroll
@@ -202,10 +206,13 @@ int grid_of(int64_t n, int block) {
 template <int K>
 hipError_t isect_fwd(const IntersectArgs& a, bool fixed, hipStream_t s) {
   constexpr int B = prim_block<K>();
+  const dim3 grid(grid_of(a.a.count, B));
   if (fixed)
-    hipLaunchKernelGGL((k_intersect_fwd<K, true>), dim3(grid_of(a.a.count, B)), dim3(B), 0, s, a);
+    hipLaunchKernelGGL((k_intersect_fwd<K, true, true>), grid, dim3(B), 0, s, a);
+  else if (a.rows_vec)
+    hipLaunchKernelGGL((k_intersect_fwd<K, false, true>), grid, dim3(B), 0, s, a);
   else
-    hipLaunchKernelGGL((k_intersect_fwd<K, false>), dim3(grid_of(a.a.count, B)), dim3(B), 0, s, a);
+    hipLaunchKernelGGL((k_intersect_fwd<K, false, false>), grid, dim3(B), 0, s, a);
   return hipGetLastError();
 }
 
