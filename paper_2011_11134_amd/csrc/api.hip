@@ -503,7 +503,8 @@ int dgal_iou_backward(dgal_ctx* ctx, int32_t mode, dgal_polys a, dgal_polys b,
                                    grad_b_z, s, sh);
     };
     // a block whose grid is its row groups has one shape: nothing to choose
-    if (dgal::matrix_bwd_split(ctx->v, a_off != nullptr, a.count)) return launch(dgal::LaunchShape());
+    if (dgal::matrix_bwd_split(ctx->v, a_off != nullptr, reg_k(a.kmax, b.kmax), a.count, b.count))
+      return launch(dgal::LaunchShape());
     auto key = [&] { return matrix_key(kTuneMatrixBwd, a, b, a_off, nseg); };
     return run_tuned(ctx, key, matrix_bwd_shapes, s, launch);
   }

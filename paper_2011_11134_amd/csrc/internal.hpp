@@ -226,15 +226,26 @@ int matrix_backward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_
 
 constexpr int kGroupRows = 8;  // rows of a row group of the matrix backward
 
-// Whether the matrix backward gives each row group a workgroup (its grid is then
-// the row groups, whatever the launch shape).
-// One block of at most one round of workgroups' row groups: a workgroup a
-// group, whose wavefronts take its steps in turn (a group of a wide block is
-// several, one after the other in a single wavefront: 300 x 4000 34 us, 15
-// so; 4096 x 4096 38 and 20; groups of one step, 1733 x 301: the same).
-// More groups than that fill the chip with a wavefront each.
-inline bool matrix_bwd_split(const CtxView& ctx, bool segmented, int64_t rows) {
-  return !segmented && (rows + kGroupRows - 1) / kGroupRows <= (int64_t)ctx.cus * 4;
+// Whether the matrix backward gives each row group a workgroup, whose wavefronts
+// take its steps in turn (its grid is then the row groups, whatever the launch
+// shape), or a wavefront.  A group of a wide block is several steps, one after
+// the other in a single wavefront; a group of one step leaves the workgroup's
+// other wavefronts idle, which costs nothing while all groups are resident at
+// once (4 workgroups a CU).  So: up to that many groups; at K = 4, whose
+// workgroups are four wavefronts (two at K = 8), also from 2,048 columns.
+// In us, a wavefront / a workgroup:
+//   up to 1,024 groups       300 x 4000 34 / 15, 4096 x 4096 38 / 20, 1733 x 301
+//                            the same, 4096 self pairs 30 / 14
+//   more, narrow blocks      20000 x 300 15.7 / 22.7 (3D 40 / 42), 60000 x 1000
+//                            49 / 59 (3D 125 / 109), 100000 x 50 48 / 68
+//   more, wide blocks        8200 x 4096 39 / 32.5 (3D 66 / 45), 30000 x 2000 47
+//                            / 40 (3D 100 / 70), 34000 x 4096 95 / 77, 8200 self
+//                            pairs 57 / 33, 34000 510 / 384
+//   K = 8                    12000 x 4096 51 / 52, 16384 x 4096 54 / 62
+inline bool matrix_bwd_split(const CtxView& ctx, bool segmented, int K, int64_t rows,
+                             int64_t cols) {
+  return !segmented && ((rows + kGroupRows - 1) / kGroupRows <= (int64_t)ctx.cus * 4 ||
+                        (K == 4 && cols >= 2048));
 }
 
 // The allocation-free forward: dgal_iou_matrix with its work list, tile state

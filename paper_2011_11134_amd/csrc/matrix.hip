@@ -30,8 +30,8 @@
 // the lower index first, so the row role of either entry is that pair's
 // gradient for the row's box, weighted by both entries' upstream gradients;
 // for two different sets the column gradients are added with global atomics, a
-// row's floats on consecutive lanes.  A block of few row groups gives each a
-// workgroup, whose wavefronts take its steps in turn.
+// row's floats on consecutive lanes.  A single block of few or wide row groups
+// gives each a workgroup, whose wavefronts take its steps in turn.
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -1060,7 +1060,7 @@ struct BwdArgs {
   SegArgs seg;
   PolyArgs a, b;
   int64_t single_groups;
-  bool split;  // one block of few row groups: a workgroup each
+  bool split;  // a workgroup for each row group (matrix_bwd_split)
   const float* grad;
   const int64_t* pair_id;
   const uint8_t* s_nx;
@@ -1652,7 +1652,7 @@ int matrix_backward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_
     constexpr int KK = decltype(k)::value;
     constexpr bool FX = decltype(fx)::value, ZZ = decltype(z)::value;
     int64_t grid = (int64_t)ctx.cus * (shape.bwd_mult > 0 ? shape.bwd_mult : 8);
-    m.split = matrix_bwd_split(ctx, segmented, a.count);
+    m.split = matrix_bwd_split(ctx, segmented, K, a.count, b.count);
     if (m.split)
       grid = single_groups;
     else if (!segmented)
