@@ -271,16 +271,17 @@ __device__ __forceinline__ void divmod(int64_t v, int64_t d, int64_t& q, int64_t
 }
 
 // ---- the cull pass ----------------------------------------------------
-// Survivor masks and counts, in units of kUnitRows rows x one tile column of
-// a segment.  The output's initial values are written by the list pass.
-constexpr int kUnitRows = kCullBlock;  // 64 rows a wavefront
+// Survivor masks and counts, in units of 256 or 64 rows x one tile column of a
+// segment.  The output's initial values are written by the list pass.
+// 64 rows a wavefront, or (words) the same 64 rows for all of them
+constexpr int unit_rows_of(bool words) { return words ? 64 : kCullBlock; }
 constexpr int kBins = 32;              // bins per axis of the masks' broad phase
 constexpr int kSparse = 16;            // most candidates of a word tested one by one
 constexpr int kFillStep = 4 * kCullBlock;  // values a fill workgroup stores at once
 
 // The pass's work in one segment (none where the segment is rejected).
-__device__ __forceinline__ int64_t mask_units_of(const Segment& g, int rl) {
-  return (g.ok && g.na > 0 && g.nb > 0) ? (g.na + kUnitRows - 1) / kUnitRows * col_tiles_of(g, rl)
+__device__ __forceinline__ int64_t mask_units_of(const Segment& g, int rl, int unit_rows) {
+  return (g.ok && g.na > 0 && g.nb > 0) ? (g.na + unit_rows - 1) / unit_rows * col_tiles_of(g, rl)
                                         : 0;
 }
 __device__ __forceinline__ int64_t fill_units_of(const Segment& g, const float* iou) {
@@ -450,7 +451,7 @@ __device__ __forceinline__ int bin_of(float v, float lo, float scale) {
   return (int)fminf(fmaxf((v - lo) * scale, 0.f), (float)(kBins - 1));
 }
 
-template <bool Z3, int C>
+template <bool Z3, int C, bool WORDS>
 struct MaskLds {
   float4 xy[C];                         // the columns' bounds x0, y0, x1, y1
   float2 z[Z3 ? C : 1];                 // and z-extents, the upper end lowered
@@ -459,10 +460,12 @@ struct MaskLds {
   // in bin kBins - 1 - b or above
   uint64_t bm[Z3 ? 3 : 2][C / 64][2 * kBins];
   float2 bins[Z3 ? 3 : 2][C / 64];      // their first coordinate, and bins per unit length
+  uint32_t count[WORDS ? kCullBlock / 64 : 1][64];  // the wavefronts' survivors of a row
 };
 
-// Masks of one unit: kUnitRows rows from row r0 of segment g against the
-// columns of tile column tc; a lane holds a row.  A pair survives when its
+// Masks of one unit: its rows from row r0 of segment g against the columns of
+// tile column tc; a lane holds a row, and tests it against all words of 64
+// columns, or (WORDS) its wavefront's share of them.  A pair survives when its
 // closed boxes overlap (touching ones go to the exact kernel) and their open
 // z extents do (the closed test on upper ends lowered by one ulp): the sign
 // bits of its four (six) bound differences are all clear.  Only the pairs
@@ -480,16 +483,18 @@ struct MaskLds {
 // on c5, 7.5 on 4096 x 4096.  Forwards of other layouts, in us: kernels that
 // tested every pair and wrote the zeros / bins of the tile's first 64 columns
 // for all of it / so:
-//   4096 x 4096    random 39 / 30.5 / 30.5, sorted along x 38 / 34 / 32.5, in
-//                  grid order 39 / 44 / 33, a far box every 256 39 / 35 / 31,
-//                  every 64 38 / 57 / 34, a crowd (10% overlap) 80 / 72 / 70
+//   4096 x 4096    random 39 / 30.5 / 30, sorted along x 38 / 34 / 30, in grid
+//                  order 39 / 44 / 30, a far box every 256 39 / 35 / 31, every 64
+//                  38 / 57 / 34, a crowd (10% overlap) 80 / 72 / 68
+//   1000 x 1000    random 21 / 19.7 / 17, a crowd 23 / 27 / 20, a denser one (75%
+//                  overlap) 42 / 72 / 41
 //   64 3D scenes   random 156 / 114 / 114, sorted 149 / 116 / 113, far boxes
 //                  160 / 128 / 118 and 157 / 185 / 140, a crowd 357 / 302 / 302
 // Rows and columns past the block, and empty z extents, survive nothing.
-template <int K, bool FIXED, bool Z3, int R>
+template <int K, bool FIXED, bool Z3, int R, bool WORDS>
 __device__ __forceinline__ void mask_unit(const CullArgs& m, const Segment& g, int64_t tile0,
                                           int64_t r0, int64_t tc,
-                                          MaskLds<Z3, kTilePairs / R>& s) {
+                                          MaskLds<Z3, kTilePairs / R, WORDS>& s) {
   constexpr int C = kTilePairs / R, W = C / 64, D = Z3 ? 3 : 2, WAVES = kCullBlock / 64;
   constexpr int kUnroll = Z3 ? 4 : 8;
   constexpr int RL = R == 4 ? 2 : (R == 8 ? 3 : 4);
@@ -543,8 +548,8 @@ __device__ __forceinline__ void mask_unit(const CullArgs& m, const Segment& g, i
   }
   __syncthreads();
 
-  const int64_t row = r0 + wave * 64 + lane;  // in the segment
-  if (r0 + wave * 64 >= g.na) return;         // uniform in the wavefront
+  const int64_t row = r0 + (WORDS ? 0 : wave * 64) + lane;  // in the segment
+  if (!WORDS && r0 + wave * 64 >= g.na) return;  // uniform in the wavefront
   Bounds rb = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (row < g.na) rb = box_bounds<K, FIXED, Z3>(m.a, g.a0 + row);
   const bool live = row < g.na && !(Z3 && !(rb.hi > rb.lo));
@@ -556,7 +561,9 @@ __device__ __forceinline__ void mask_unit(const CullArgs& m, const Segment& g, i
   uint64_t* state = m.tile_mask + u * kMaskWords + (lane & (R - 1));
   uint32_t n = 0u;
 #pragma unroll
-  for (int w = 0; w < W; ++w) {
+  for (int i = 0; i < (WORDS ? (W + WAVES - 1) / WAVES : W); ++i) {
+    const int w = WORDS ? wave + i * WAVES : i;
+    if (WORDS && w >= W) break;  // uniform
     uint64_t keep = 0ull;
     if (w * 64 < nc) {  // uniform
       uint64_t cand = live ? ~0ull : 0ull;
@@ -605,6 +612,14 @@ __device__ __forceinline__ void mask_unit(const CullArgs& m, const Segment& g, i
     n += (uint32_t)__popcll(keep);
     if (have) state[w * R] = keep;
   }
+  if constexpr (WORDS) {
+    s.count[wave][lane] = n;
+    __syncthreads();
+    if (wave != 0) return;
+    n = 0u;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) n += s.count[w][lane];
+  }
   // the tile's count: its R rows are R neighbouring lanes
 #pragma unroll
   for (int d = 1; d < R; d <<= 1) n += (uint32_t)__shfl_xor((int)n, d);
@@ -619,16 +634,17 @@ __device__ __forceinline__ void mask_unit(const CullArgs& m, const Segment& g, i
   }
 }
 
-template <int K, bool FIXED, bool Z3, int R>
+template <int K, bool FIXED, bool Z3, int R, bool WORDS>
 __global__ __launch_bounds__(kCullBlock)
 __attribute__((amdgpu_waves_per_eu(R == 4 || !Z3 ? 5 : 7))) void k_matrix_cull(CullArgs m) {
   static_assert(R == 4 || R == 8 || R == 16, "tile rows");
   constexpr int C = kTilePairs / R;
   constexpr int RL = R == 4 ? 2 : (R == 8 ? 3 : 4);
-  __shared__ MaskLds<Z3, C> s_mask;
+  constexpr int UNIT_ROWS = unit_rows_of(WORDS);
+  __shared__ MaskLds<Z3, C, WORDS> s_mask;
   __shared__ SegScan s_scan;
   const bool segmented = m.seg.a_off != nullptr;
-  auto units_of = [&](const Segment& g) { return mask_units_of(g, RL); };
+  auto units_of = [&](const Segment& g) { return mask_units_of(g, RL, UNIT_ROWS); };
   UnitSeg us = {load_segment(m.seg, 0), 0, 0};
   int64_t total = m.single_units;
   if (segmented) {
@@ -641,7 +657,7 @@ __attribute__((amdgpu_waves_per_eu(R == 4 || !Z3 ? 5 : 7))) void k_matrix_cull(C
     const int64_t nct = col_tiles_of(us.g, RL);
     int64_t rc, tc;
     divmod(u - us.unit0, nct, rc, tc);
-    mask_unit<K, FIXED, Z3, R>(m, us.g, us.tile0, rc * kUnitRows, tc, s_mask);
+    mask_unit<K, FIXED, Z3, R, WORDS>(m, us.g, us.tile0, rc * UNIT_ROWS, tc, s_mask);
   }
 }
 
@@ -939,20 +955,26 @@ __device__ __forceinline__ bool locate(const SegArgs& sa, int64_t pid, SegCache&
 // rows are found by their row groups, which only the accepted segments own: a
 // rejected one's offsets need not be in order, so a row's place in a_off does
 // not tell its segment.
-__device__ __forceinline__ void write_diagonals(const SegArgs& a, float* iou) {
+__device__ __forceinline__ void write_diagonals(const SegArgs& a, int64_t groups, float* iou) {
   const bool segmented = a.a_off != nullptr;
-  const int64_t groups = segmented ? a.group_prefix[a.nseg]
-                                   : (a.a_count + kGroupRows - 1) / kGroupRows;
   const int64_t threads = (int64_t)gridDim.x * kExactBlock;
   for (int64_t t0 = ((int64_t)gridDim.x - 1 - blockIdx.x) * kExactBlock + (threadIdx.x & ~63);
        t0 < groups * kGroupRows; t0 += threads) {  // the wavefront's 64 rows
     const int64_t u = (t0 + (threadIdx.x & 63)) / kGroupRows;
-    int s = segmented ? wave_find_segment(a.group_prefix, a.nseg, wave_first(t0 / kGroupRows)) : 0;
+    const int s0 =
+        segmented ? wave_find_segment(a.group_prefix, a.nseg, wave_first(t0 / kGroupRows)) : 0;
     if (u >= groups) continue;
-    if (segmented && u >= a.group_prefix[s + 1]) s = find_segment(a.group_prefix, a.nseg, u);
-    const Segment g = load_segment(a, s);
-    const int64_t r = (u - (segmented ? a.group_prefix[s] : 0)) * kGroupRows +
-                      (threadIdx.x & (kGroupRows - 1));
+    Segment g = load_segment(a, s0);
+    int64_t first = 0;
+    if (segmented) {
+      first = a.group_prefix[s0];
+      if (u >= a.group_prefix[s0 + 1]) {
+        const int s = find_segment(a.group_prefix, a.nseg, u);
+        g = load_segment(a, s);
+        first = a.group_prefix[s];
+      }
+    }
+    const int64_t r = (u - first) * kGroupRows + (threadIdx.x & (kGroupRows - 1));
     if (g.ok && r < g.na) iou[g.out0 + r * (g.nb + 1)] = 1.f;
   }
 }
@@ -965,6 +987,10 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_matrix_exact(ExactArgs m) {
   __shared__ uint16_t s_cd[CAP * kExactBlock];
   const int tid = threadIdx.x;
   int64_t n = *m.count;
+  int64_t groups = 0;  // row groups with a diagonal
+  if (m.seg.self_pairs)
+    groups = m.seg.a_off != nullptr ? m.seg.group_prefix[m.seg.nseg]
+                                    : (m.seg.a_count + kGroupRows - 1) / kGroupRows;
   if (n > m.capacity) {  // uniform; an overflow
     n = m.capacity;
     int64_t nt = m.seg.tile_prefix != nullptr ? m.seg.tile_prefix[m.seg.nseg] : m.single_tiles;
@@ -975,7 +1001,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_matrix_exact(ExactArgs m) {
       if (room < m.tile_count[t]) m.tile_count[t] = (int32_t)room;
     }
   }
-  if (m.seg.self_pairs) write_diagonals(m.seg, m.iou);
+  if (groups > 0) write_diagonals(m.seg, groups, m.iou);
   // each wavefront a contiguous range of entries, 64 at a time: consecutive
   // entries mostly share a segment, which is then searched once
   const int64_t wid = ((int64_t)blockIdx.x * kExactBlock + tid) >> 6;
@@ -1496,6 +1522,14 @@ int matrix_forward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_t
   c.tile_prefix = pre;
   c.group_prefix = segmented ? pre + (kMaxSeg + 1) : nullptr;
   c.err = ctx.err;
+  // up to a 256-row unit a CU (4096 x 4096; of segments the output's size tells),
+  // units of 64 rows whose words the wavefronts share: more workgroups, each a
+  // quarter of the tests, where the chip would be idle and the busiest unit is
+  // the pass.  256 / 64 rows, the whole forward in us: 2000 x 301 16.8 / 14.0,
+  // in a crowd 23.8 / 18.4; 4096 x 4096 30.6 / 30.1, in grid order 32.7 / 30.2;
+  // 8 scenes of 50..2000 33.2 / 31.5.  Past it the columns' bins, made four times
+  // as often, cost more: 5000 x 5000 36.9 / 38.2, 64 scenes 114 / 132.
+  const bool words = (segmented ? out_size : a.count * b.count) <= (int64_t)ctx.cus * 65536;
   // the units' workgroups; with segments, whose sizes are on the device, they
   // walk the units in grid strides
   int64_t cull_grid = (int64_t)ctx.cus * (shape.cull_mult > 0 ? shape.cull_mult : 8);
@@ -1503,7 +1537,7 @@ int matrix_forward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_t
     c.single_units = 0;
     cull_grid = std::max<int64_t>(1, std::min(cull_grid, saved->tile_capacity));
   } else {
-    c.single_units = ceil_div(a.count, kUnitRows) * ceil_div(b.count, kTilePairs / R);
+    c.single_units = ceil_div(a.count, unit_rows_of(words)) * ceil_div(b.count, kTilePairs / R);
     cull_grid = std::min(cull_grid, c.single_units);
   }
   ListArgs li;
@@ -1545,9 +1579,14 @@ int matrix_forward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_t
     constexpr bool FX = decltype(fx)::value, ZZ = decltype(z)::value;
     prof_begin(ctx.prof, stream);
     const dim3 cg((unsigned)cull_grid), cb(kCullBlock);
-    if (R == 4) hipLaunchKernelGGL((k_matrix_cull<KK, FX, ZZ, 4>), cg, cb, 0, stream, c);
-    else if (R == 16) hipLaunchKernelGGL((k_matrix_cull<KK, FX, ZZ, 16>), cg, cb, 0, stream, c);
-    else hipLaunchKernelGGL((k_matrix_cull<KK, FX, ZZ, 8>), cg, cb, 0, stream, c);
+    auto cull = [&](auto rows) {
+      constexpr int RR = decltype(rows)::value;
+      if (words) hipLaunchKernelGGL((k_matrix_cull<KK, FX, ZZ, RR, true>), cg, cb, 0, stream, c);
+      else hipLaunchKernelGGL((k_matrix_cull<KK, FX, ZZ, RR, false>), cg, cb, 0, stream, c);
+    };
+    if (R == 4) cull(std::integral_constant<int, 4>{});
+    else if (R == 16) cull(std::integral_constant<int, 16>{});
+    else cull(std::integral_constant<int, 8>{});
     prof_end(ctx.prof, "k_matrix_cull", stream);
     if (saved->tile_capacity > kListDirect) {
       const int64_t chunks = ceil_div(saved->tile_capacity, kScanChunk);
@@ -1560,8 +1599,10 @@ int matrix_forward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_t
     }
     // the list's workgroups first, then the fill's, a step each up to the
     // launch's limit on threads
+    // (8 tiles are a workgroup's step: 300 x 300 boxes that mostly overlap take
+    // 26 us with twice as many, 21.5 so)
     li.list_blocks = std::max<int64_t>(
-        1, std::min<int64_t>((int64_t)ctx.cus * 2, ceil_div(saved->tile_capacity, 16)));
+        1, std::min<int64_t>((int64_t)ctx.cus * 2, ceil_div(saved->tile_capacity, 8)));
     const int64_t fill = ceil_div((segmented ? out_size : a.count * b.count) + 3, kFillStep);
     prof_begin(ctx.prof, stream);
     hipLaunchKernelGGL(k_matrix_list,

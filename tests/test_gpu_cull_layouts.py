@@ -31,39 +31,53 @@ def _lay(kind, rng, xy):
     return xy
 
 
+KINDS = ["sorted", "far_every_64", "far_one_word", "crowd", "half_crowd", "infinite"]
+
+
+def _check(dg, rng, kind, rows, na, nb, self_pairs, z, capacity):
+    a = _lay(kind, rng, _boxes(rng, na, 40.0))
+    b = a if self_pairs else _lay(kind, rng, _boxes(rng, nb, 40.0))
+    nb = len(b)
+    az = bz = None
+    if z:
+        heights = lambda n: [rng.uniform(-2, 1, n).astype(np.float32)]
+        az = heights(na)
+        az.append(az[0] + rng.uniform(-0.2, 2, na).astype(np.float32))  # some empty
+        bz = az
+        if not self_pairs:
+            bz = heights(nb)
+            bz.append(bz[0] + rng.uniform(-0.2, 2, nb).astype(np.float32))
+    t = lambda v: None if v is None else tuple(dev_t(x) for x in v)
+    seg = dg.segments(na, nb, None)
+    sv = dg.SavedPairs(capacity, 8, seg[5], torch.device("cuda"), tile_rows=rows)
+    more = {"self_pairs": True} if self_pairs else {"b_z": t(bz)}
+    _, saved, _ = dg.iou_matrix(dev_t(a), None if self_pairs else dev_t(b), a_z=t(az), save=True,
+                                seg=seg, saved=sv, **more)
+    pid, _, _, _ = _saved_entries(saved)
+    with np.errstate(invalid="ignore"):
+        keep = _survivors(a, b, az, bz)
+    if self_pairs:
+        np.fill_diagonal(keep, False)
+    want = np.nonzero(keep.ravel())[0]
+    assert len(want) > 0 and int(saved.count.item()) == len(want)
+    assert np.array_equal(np.sort(pid), want), (kind, rows, z)
+
+
 @pytest.mark.parametrize("rows", [4, 8, 16])
-@pytest.mark.parametrize("kind", ["sorted", "far_every_64", "far_one_word", "crowd", "half_crowd",
-                                  "infinite"])
+@pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("self_pairs", [False, True])
 def test_survivors(kind, rows, self_pairs):
     import paper_2011_11134_amd as dg
     rng = np.random.default_rng(rows + len(kind))
-    na, nb = 300, 583
-    a = _lay(kind, rng, _boxes(rng, na, 40.0))
-    b = a if self_pairs else _lay(kind, rng, _boxes(rng, nb, 40.0))
-    nb = len(b)
     for z in (False, True):
-        az = bz = None
-        if z:
-            heights = lambda n: [rng.uniform(-2, 1, n).astype(np.float32)]
-            az = heights(na)
-            az.append(az[0] + rng.uniform(-0.2, 2, na).astype(np.float32))  # some empty
-            bz = az
-            if not self_pairs:
-                bz = heights(nb)
-                bz.append(bz[0] + rng.uniform(-0.2, 2, nb).astype(np.float32))
-        t = lambda v: None if v is None else tuple(dev_t(x) for x in v)
-        seg = dg.segments(na, nb, None)
-        sv = dg.SavedPairs(na * nb, 8, seg[5], torch.device("cuda"), tile_rows=rows)
-        ta = dev_t(a)
-        more = {"self_pairs": True} if self_pairs else {"b_z": t(bz)}
-        _, saved, _ = dg.iou_matrix(ta, None if self_pairs else dev_t(b), a_z=t(az), save=True,
-                                    seg=seg, saved=sv, **more)
-        pid, _, _, _ = _saved_entries(saved)
-        with np.errstate(invalid="ignore"):
-            keep = _survivors(a, b, az, bz)
-        if self_pairs:
-            np.fill_diagonal(keep, False)
-        want = np.nonzero(keep.ravel())[0]
-        assert len(want) > 0 and int(saved.count.item()) == len(want)
-        assert np.array_equal(np.sort(pid), want), (kind, rows, z)
+        _check(dg, rng, kind, rows, 300, 583, self_pairs, z, 300 * 583)
+
+
+@pytest.mark.parametrize("rows,kind", [(4, "half_crowd"), (8, "sorted"), (8, "far_every_64"),
+                                       (8, "half_crowd"), (16, "infinite")])
+@pytest.mark.parametrize("z", [False, True])
+def test_survivors_of_a_large_block(kind, rows, z):
+    """Past 16.8 M pairs: units of 256 rows, whose last one here is 25 rows."""
+    import paper_2011_11134_amd as dg
+    rng = np.random.default_rng(rows + len(kind))
+    _check(dg, rng, kind, rows, 4121, 4099, False, z, 1 << 23)
