@@ -177,12 +177,47 @@ __device__ __forceinline__ void wave_sync() {
 // negp, negq: bit 8 i + j set when the value is negative, as the fp32 table's.
 // One lane of a wavefront needs this on 8% of the wavefronts of the 3..8-gon
 // workload; walking its 64 entries in that lane alone took 10 us, which
-// ended every launch of one round (262,144 pairs: 38 us, 25.7 now).
+// ended every launch of one round (262,144 pairs: 38 us, 25.7 now).  Where more
+// than kOwnSigns lanes need it (identical polygons, shared corners), each walks
+// its own entries, 64 steps for all of them where the wavefront takes about two a
+// lane (1,048,576 pairs of 3..8-gons, all identical: 194 us a lane at a time, 141
+// so; half of them 137 and 146; they meet at 36 lanes, for 8-gons at 42).
+constexpr int kOwnSigns = 38;
 template <int BLOCK>
 __device__ __forceinline__ void exact_signs8(uint64_t need, const float2* p_col,
                                              const float2* q_col, int n1, int n2, uint64_t& negp,
                                              uint64_t& negq) {
   const int lane = threadIdx.x & 63, i = lane >> 3, j = lane & 7;
+  if (__popcll(need) > kOwnSigns) {  // uniform
+    if ((need >> lane) & 1u) {
+      negp = 0ull;
+      negq = 0ull;
+      float2 p = p_col[lane];
+#pragma unroll 1
+      for (int a = 0; a < 8; ++a) {  // (slots at and past the count repeat vertex 0)
+        const int an = a + 1 < n1 ? a + 1 : 0;
+        const float2 pn = p_col[an * BLOCK + lane];
+        const bool tie_p = (p.y != pn.y) ? (p.y > pn.y) : (pn.x > p.x);
+        uint32_t np = 0u, nq = 0u;
+        float2 q = q_col[lane];
+#pragma unroll 1
+        for (int b = 0; b < 8; ++b) {
+          const int bn = b + 1 < n2 ? b + 1 : 0;
+          const float2 qn = q_col[bn * BLOCK + lane];
+          const bool tie_q = (qn.y != q.y) ? (qn.y > q.y) : (q.x > qn.x);
+          const double op = orient64(q.x, q.y, qn.x, qn.y, p.x, p.y);
+          const double oq = orient64(p.x, p.y, pn.x, pn.y, q.x, q.y);
+          np |= (op > 0.0 || (op == 0.0 && tie_q)) ? 0u : 1u << b;
+          nq |= (oq > 0.0 || (oq == 0.0 && tie_p)) ? 0u : 1u << b;
+          q = qn;
+        }
+        negp |= (uint64_t)np << (8 * a);
+        negq |= (uint64_t)nq << (8 * a);
+        p = pn;
+      }
+    }
+    return;
+  }
   while (need != 0ull) {  // uniform
     const int l = __builtin_ctzll(need);
     need &= need - 1ull;
