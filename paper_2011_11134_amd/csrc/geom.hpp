@@ -796,7 +796,8 @@ __device__ __forceinline__ const float2& at(const float2* col, uint32_t off) {
 //   A gets G - dL/de - dL/dw, B gets dL/de, C gets dL/dw - dL/df, D gets dL/df.
 // t and 1/den come from the caller (0 for a polygon vertex, whose slots are
 // all A: it adds G to A and zeros to the aliases, which are written first).
-// `live` false leaves the accumulators as they are.
+// MASKED: `live` false leaves the accumulators as they are.
+template <bool MASKED = false>
 __device__ __forceinline__ void route_slot(float Gx, float Gy, float t, float idn, uint32_t oa,
                                            uint32_t ob, uint32_t oc, uint32_t od,
                                            float2* __restrict__ s_v, float2* __restrict__ s_g,
@@ -819,12 +820,11 @@ __device__ __forceinline__ void route_slot(float Gx, float Gy, float t, float id
   td.y += gfy;
   ta.x += Gx - gex - gwx;
   ta.y += Gy - gey - gwy;
-  if (live) {
-    at(s_g, ob) = tb;
-    at(s_g, oc) = tc;
-    at(s_g, od) = td;
-    at(s_g, oa) = ta;
-  }
+  if (MASKED && !live) return;
+  at(s_g, ob) = tb;
+  at(s_g, oc) = tc;
+  at(s_g, od) = td;
+  at(s_g, oa) = ta;
 }
 
 // t and 1/den of the vertex in slots (oa, ob, oc, od); its position is
@@ -938,8 +938,9 @@ __device__ __forceinline__ void pair_backward(const Poly<K>& P, int n1, const Po
       acc += has ? term : 0.f;
     }
     // d(2I)/dX_r = (y_r+1 - y_r-1, x_r-1 - x_r+1)
-    route_slot(live ? nxt.y - prev.y : 0.f, live ? prev.x - nxt.x : 0.f, live ? gc.t : 0.f,
-               live ? gc.idn : 0.f, gc.oa, gc.ob, gc.oc, gc.od, s_v, s_g, K == 4 || live);
+    route_slot<K == 8>(live ? nxt.y - prev.y : 0.f, live ? prev.x - nxt.x : 0.f,
+                       live ? gc.t : 0.f, live ? gc.idn : 0.f, gc.oa, gc.ob, gc.oc, gc.od, s_v,
+                       s_g, live);
     last = live ? cur : last;
     prev = cur;
     cur = nxt;
