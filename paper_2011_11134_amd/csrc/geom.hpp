@@ -796,12 +796,9 @@ __device__ __forceinline__ const float2& at(const float2* col, uint32_t off) {
 //   A gets G - dL/de - dL/dw, B gets dL/de, C gets dL/dw - dL/df, D gets dL/df.
 // t and 1/den come from the caller (0 for a polygon vertex, whose slots are
 // all A: it adds G to A and zeros to the aliases, which are written first).
-// MASKED: `live` false leaves the accumulators as they are.
-template <bool MASKED = false>
 __device__ __forceinline__ void route_slot(float Gx, float Gy, float t, float idn, uint32_t oa,
                                            uint32_t ob, uint32_t oc, uint32_t od,
-                                           float2* __restrict__ s_v, float2* __restrict__ s_g,
-                                           bool live = true) {
+                                           float2* __restrict__ s_v, float2* __restrict__ s_g) {
   const float2 a = at(s_v, oa), b = at(s_v, ob), cc = at(s_v, oc), d = at(s_v, od);
   float2 ta = at(s_g, oa), tb = at(s_g, ob), tc = at(s_g, oc), td = at(s_g, od);
   const float ex = b.x - a.x, ey = b.y - a.y, fx = d.x - cc.x, fy = d.y - cc.y;
@@ -820,7 +817,6 @@ __device__ __forceinline__ void route_slot(float Gx, float Gy, float t, float id
   td.y += gfy;
   ta.x += Gx - gex - gwx;
   ta.y += Gy - gey - gwy;
-  if (MASKED && !live) return;
   at(s_g, ob) = tb;
   at(s_g, oc) = tc;
   at(s_g, od) = td;
@@ -920,10 +916,7 @@ __device__ __forceinline__ void pair_backward(const Poly<K>& P, int n1, const Po
   // rolling window needs no copies and a step's LDS reads (the next vertex's
   // polygon slots, this one's accumulators) are in flight together: a masked
   // slot routes a zero gradient with t = 1/den = 0 (its rebuilt point, from a
-  // padding code, may be far off or infinite and is never multiplied in).  At
-  // K = 8, where how many slots a lane visits depends on the wavefront's other
-  // pairs, a masked slot is not stored either: next to an infinite or NaN
-  // vertex its zeros would be NaN.
+  // padding code, may be far off or infinite and is never multiplied in).
 #pragma unroll
   for (int r = 1; r < CAP; ++r) {
     if (K == 8 && __ballot(r < m) == 0ull) break;  // uniform
@@ -938,9 +931,8 @@ __device__ __forceinline__ void pair_backward(const Poly<K>& P, int n1, const Po
       acc += has ? term : 0.f;
     }
     // d(2I)/dX_r = (y_r+1 - y_r-1, x_r-1 - x_r+1)
-    route_slot<K == 8>(live ? nxt.y - prev.y : 0.f, live ? prev.x - nxt.x : 0.f,
-                       live ? gc.t : 0.f, live ? gc.idn : 0.f, gc.oa, gc.ob, gc.oc, gc.od, s_v,
-                       s_g, live);
+    route_slot(live ? nxt.y - prev.y : 0.f, live ? prev.x - nxt.x : 0.f, live ? gc.t : 0.f,
+               live ? gc.idn : 0.f, gc.oa, gc.ob, gc.oc, gc.od, s_v, s_g);
     last = live ? cur : last;
     prev = cur;
     cur = nxt;
@@ -988,6 +980,13 @@ __device__ __forceinline__ void pair_backward(const Poly<K>& P, int n1, const Po
   // read back: dL/dv = gI / 2 * (routed shoelace terms) + gA * dA/dv, with
   // dA/dv = (y+ - y-, x- - x+) / 2 over the polygon's own neighbours
   const float hI = 0.5f * gI, h1a = 0.5f * gA1, h2a = 0.5f * gA2;
+  // Beside an infinite or NaN vertex the masked slots' zeros are NaN, and how
+  // many of them a lane visits at K = 8 depends on the wavefront's other pairs.
+  // The padding code routes them to the first and last vertices: where the
+  // intersection does not move the IoU (always so beside such a vertex) their
+  // sums are left out.  (Skipping the masked slots' stores instead took 1% more
+  // and moved the sums' rounding, routing them to vertex 0 of P 2 to 5%.)
+  const bool flat = hI == 0.f;
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     float2 pn, pp, qn, qp;
@@ -1004,7 +1003,11 @@ __device__ __forceinline__ void pair_backward(const Poly<K>& P, int n1, const Po
       qn = s_v[(K + kn2) * BLOCK];
       qp = s_v[(K + kp2) * BLOCK];
     }
-    const float2 tp = s_g[k * BLOCK], tq = s_g[(K + k) * BLOCK];
+    float2 tp = s_g[k * BLOCK], tq = s_g[(K + k) * BLOCK];
+    if (K == 8 && (k == 0 || k == K - 1) && flat) {
+      tp = make_float2(0.f, 0.f);
+      tq = make_float2(0.f, 0.f);
+    }
     gP[k] = (FIXED || k < n1) ? make_float2(fmaf(hI, tp.x, h1a * (pn.y - pp.y)),
                                             fmaf(hI, tp.y, h1a * (pp.x - pn.x)))
                               : make_float2(0.f, 0.f);

@@ -11,17 +11,18 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("z3", [False, True])
+@pytest.mark.parametrize("side", ["a", "b"])
 @pytest.mark.parametrize("kmax,bad", [(8, "inf"), (8, "nan"), (8, "far"), (6, "inf")])
-def test_gradient_of_a_pair_alone_and_in_a_batch(kmax, bad, z3):
+def test_gradient_of_a_pair_alone_and_in_a_batch(kmax, bad, side, z3):
     import paper_2011_11134_amd as dg
     rng = np.random.default_rng(kmax)
     n = 96  # a whole wavefront and half of one
     a, an = synth.workloads.random_convex(rng, n, kmin=kmax, kmax=kmax)
     b, bn = synth.workloads.random_convex(rng, n, kmin=kmax, kmax=kmax)
-    special = np.arange(3, n, 7)
+    special = np.arange(3, n, 5)
     value = {"inf": np.inf, "nan": np.nan, "far": 3e38}[bad]
-    # one vertex of the second polygon, and every second pair too far to meet
-    b[special, kmax - 1] = value
+    # one vertex of one polygon (each in turn), every second pair too far to meet
+    (a if side == "a" else b)[special, np.arange(len(special)) % kmax] = value
     a[special[::2]] += np.float32(100.0)
     z = None
     if z3:
@@ -46,5 +47,7 @@ def test_gradient_of_a_pair_alone_and_in_a_batch(kmax, bad, z3):
             if whole is not None:
                 assert np.array_equal(whole[i], alone[0], equal_nan=True), (i, whole[i], alone[0])
     # an empty intersection moves nothing: the finite polygon's gradient is 0
+    # (vertex 0 of the first polygon, the origin of the pair's frame, aside)
     empty = special[nx[special.tolist()].cpu().numpy() == 0]
-    assert len(empty) and not batch[0][empty].any()
+    empty = empty[np.isfinite(a[empty, 0]).all(1)]
+    assert len(empty) and not batch[1 if side == "a" else 0][empty].any()
