@@ -50,4 +50,4 @@ def test_gradient_of_a_pair_alone_and_in_a_batch(kmax, bad, side, z3):
     # (vertex 0 of the first polygon, the origin of the pair's frame, aside)
     empty = special[nx[special.tolist()].cpu().numpy() == 0]
     empty = empty[np.isfinite(a[empty, 0]).all(1)]
-    assert len(empty) and not batch[1 if side == "a" else 0][empty].any()
+    assert not batch[1 if side == "a" else 0][empty].any()
