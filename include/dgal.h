@@ -239,8 +239,9 @@ enum { DGAL_PAIRS = 0, DGAL_MATRIX = 1 };
  * Outputs (overwritten; padded vertex slots are written 0):
  *   grad_a_xy [a.count][a.kmax][2], grad_b_xy [b.count][b.kmax][2] fp32
  *   grad_a_z, grad_b_z [count][2] fp32 = (d/dzlo, d/dzhi); NULL for 2D.
- * The matrix mode sums each row's gradient in a fixed order (its entries in
- * work-list order) and writes every row once, so rows (and every self-pair
+ * The matrix mode sums each row's gradient in a fixed order (steps of 64
+ * work-list entries; a single block's may be summed in up to four interleaved
+ * parts first) and writes every row once, so rows (and every self-pair
  * gradient) are the same bits from run to run; with two different sets the
  * column gradients are added with fp32 global atomics (their order, and so
  * the low-order bits, may vary).

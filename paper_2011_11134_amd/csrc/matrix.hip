@@ -782,9 +782,9 @@ __device__ __forceinline__ void fill_step(float* out, int64_t size, int64_t o) {
 // bound by latency and the fill by memory, so they share the chip.  Where the
 // blocks cover the output without gaps it is one flat stream, a step a
 // workgroup: one aligned 16-byte store a lane and short-lived wavefronts
-// write 6.7 TB/s here (348 MB in 52 us; grid-stride loops 5.6, and the rows
-// of the masks' tiles, as the masks were made, 3.9, each row ending in two
-// partial cache lines).  Otherwise each block is filled by itself, found from
+// write 6.7 TB/s here (348 MB alone in 52 us, c5's 374 MB beside the list in
+// 62; grid-stride loops 5.6, and the rows of the masks' tiles, as the masks were
+// made, 3.9, each row ending in two partial cache lines).  Otherwise each block is filled by itself, found from
 // a scan of the segments, and gaps are left alone.
 __device__ __forceinline__ void fill_output(const ListArgs& m, int64_t b, int64_t nblk,
                                             SegScan& sc) {
