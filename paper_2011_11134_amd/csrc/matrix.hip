@@ -7,7 +7,7 @@
 //   k_matrix_cull -- survivor masks and counts per tile of R rows x 2048 / R
 //     columns of one segment (R = 4, 8 or 16, chosen per call).  A lane holds a
 //     row; the pairs it tests are those whose bins on every axis overlap, found
-//     64 columns at a time from bit sets in LDS.
+//     64 columns at a time from bit sets in LDS (all 64 where those are many).
 //   k_matrix_list -- lays the work list out tile by tile, deterministically
 //     (the prefix of the tile counts, then the masks' survivors), while its
 //     other workgroups write the output's zeros as a flat stream.
@@ -16,7 +16,7 @@
 //     kept in the work list for the backward; and the self diagonal's 1s.
 // (k_scan_totals sums chunks of tile counts first where the table is too
 // large for each list workgroup to sum the counts before its own.)
-// c5 (64 scenes, 93.6 M pairs) takes 20 + 62 + 33 us; a kernel that tested every
+// c5 (64 scenes, 93.6 M pairs) takes 23 + 63 + 35 us; a kernel that tested every
 // pair and wrote the tiles' values (103 us), two scan passes (11), a fill of
 // the list (13) and the exact pass (31) took 162 with the segments' prefixes.
 // Grids walk the units or tiles of all segments, whose sizes are on the
@@ -26,8 +26,8 @@
 // that cover it are one contiguous range of the work list; each step's row
 // gradients are summed without atomics (sorted by row in LDS, each lane
 // adding up one (row, vertex) run in a fixed order) and every row is written
-// once.  Self pairs need nothing else: entries (i, k) and (k, i) are one unordered pair evaluated with
-// the lower index first, so the row role of either entry is that pair's
+// once.  Self pairs need nothing else: entries (i, k) and (k, i) are one
+// unordered pair evaluated with the lower index first, so the row role of either entry is that pair's
 // gradient for the row's box, weighted by both entries' upstream gradients;
 // for two different sets the column gradients are added with global atomics, a
 // row's floats on consecutive lanes.  A single block of few or wide row groups
@@ -479,8 +479,8 @@ struct MaskLds {
 // layout costs more than a test of every pair (a candidate alone takes some 200
 // cycles of latency, two at a time; a column of all 7 to 10 vector
 // instructions; kSparse 8 took 3% more on a 3D crowd, 24 the same).  Bound by
-// latency (the LDS reads of the tests; the busiest lane has about four): 20 us
-// on c5, 7.5 on 4096 x 4096.  Forwards of other layouts, in us: kernels that
+// latency (the LDS reads of the tests; the busiest lane has about four): 23 us
+// on c5, 7 on 4096 x 4096.  Forwards of other layouts, in us: kernels that
 // tested every pair and wrote the zeros / bins of the tile's first 64 columns
 // for all of it / so:
 //   4096 x 4096    random 39 / 30.5 / 30, sorted along x 38 / 34 / 30, in grid
