@@ -1086,7 +1086,6 @@ struct BwdArgs {
   SegArgs seg;
   PolyArgs a, b;
   int64_t single_groups;
-  bool split;  // a workgroup for each row group (matrix_bwd_split)
   const float* grad;
   const int64_t* pair_id;
   const uint8_t* s_nx;
@@ -1219,8 +1218,11 @@ __device__ __forceinline__ void add_columns(uint64_t live, const float2* stage, 
   wave_sync();  // the columns are the pair kernels' staging again
 }
 
-// SELF: self pairs (a kernel of its own: the two roles' code together spilled).
-template <int K, bool FIXED, bool Z3, bool SELF>
+// SELF: self pairs; SPLIT: a workgroup for each row group (matrix_bwd_split).
+// Kernels of their own: the roles' code together spilled, and the split as a
+// run-time switch took the others 1 to 4% (32 scenes of 2D quadrilaterals 14.5
+// us, 14.1 so; c5 44.9 and 44.5 in a graph).
+template <int K, bool FIXED, bool Z3, bool SELF, bool SPLIT>
 __global__ __launch_bounds__(bwd_block<K>())
 __attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 2))) void k_matrix_bwd(BwdArgs m) {
   constexpr int BLOCK = bwd_block<K>();
@@ -1262,8 +1264,8 @@ __attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 2))) void k_matrix_bwd(BwdArgs m
   }
 
   // split: the workgroup's wavefronts take the group's steps in turn
-  const int part = m.split ? wave : 0, parts = m.split ? WAVES : 1;
-  const int64_t u0 = m.split ? blockIdx.x : (int64_t)blockIdx.x * WAVES + wave;
+  const int part = SPLIT ? wave : 0, parts = SPLIT ? WAVES : 1;
+  const int64_t u0 = SPLIT ? blockIdx.x : (int64_t)blockIdx.x * WAVES + wave;
   for (int64_t u = u0; u < total; u += (int64_t)gridDim.x * WAVES) {
     const int s = segmented ? wave_find_segment(m.seg.group_prefix, m.seg.nseg, u) : 0;
     const int64_t tr = segmented ? u - m.seg.group_prefix[s] : u;  // row group in the segment
@@ -1379,7 +1381,7 @@ __attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 2))) void k_matrix_bwd(BwdArgs m
         add_columns<K, FIXED, Z3, BLOCK>(__ballot(rl >= 0), stage, m.gb_xy, m.b.kmax, m.gb_z);
       step_row_sums<H, BLOCK>(rl, gv, stage, acc);
     }
-    if (m.split) {  // the wavefronts' sums, in their order; one group a workgroup
+    if constexpr (SPLIT) {  // the wavefronts' sums, in their order; one group a workgroup
 #pragma unroll
       for (int j = 0; j < NACC; ++j) s_g[j * BLOCK + tid] = acc[j];
       __syncthreads();
@@ -1693,18 +1695,20 @@ int matrix_backward(const CtxView& ctx, dgal_polys a, dgal_polys b, const int64_
     constexpr int KK = decltype(k)::value;
     constexpr bool FX = decltype(fx)::value, ZZ = decltype(z)::value;
     int64_t grid = (int64_t)ctx.cus * (shape.bwd_mult > 0 ? shape.bwd_mult : 8);
-    m.split = matrix_bwd_split(ctx, segmented, K, a.count, b.count);
-    if (m.split)
+    const bool split = matrix_bwd_split(ctx, segmented, K, a.count, b.count);
+    if (split)
       grid = single_groups;
     else if (!segmented)
       grid = std::min(grid, ceil_div(single_groups, bwd_block<KK>() / 64));
     prof_begin(ctx.prof, stream);
-    if (self_pairs)
-      hipLaunchKernelGGL((k_matrix_bwd<KK, FX, ZZ, true>), dim3((unsigned)grid),
-                         dim3(bwd_block<KK>()), 0, stream, m);
-    else
-      hipLaunchKernelGGL((k_matrix_bwd<KK, FX, ZZ, false>), dim3((unsigned)grid),
-                         dim3(bwd_block<KK>()), 0, stream, m);
+    auto go = [&](auto self, auto split) {
+      hipLaunchKernelGGL((k_matrix_bwd<KK, FX, ZZ, decltype(self)::value, decltype(split)::value>),
+                         dim3((unsigned)grid), dim3(bwd_block<KK>()), 0, stream, m);
+    };
+    if (self_pairs && split) go(Bool<true>{}, Bool<true>{});
+    else if (self_pairs) go(Bool<true>{}, Bool<false>{});
+    else if (split) go(Bool<false>{}, Bool<true>{});
+    else go(Bool<false>{}, Bool<false>{});
     prof_end(ctx.prof, "k_matrix_bwd", stream);
   });
   return hipGetLastError() == hipSuccess ? DGAL_OK : DGAL_EHIP;
