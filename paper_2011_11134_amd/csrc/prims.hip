@@ -18,12 +18,12 @@ constexpr int prim_block() {
 // rectangles: 36.8 us with a row a lane, 32.4 so; 262,144 of 3..8-gons: 39.5
 // and 29).  ROWS: cap == 2K and every row 16-byte aligned; the other rows have
 // an instance of their own, and both are held to the 4 waves per SIMD that make
-// 262,144 pairs at K = 4 one round: with both forms in one kernel left alone,
+// 262,144 pairs at K = 4 one round (fixed quadrilaterals take them by themselves): with both forms in one kernel left alone,
 // triangles took 16.3 us (137 VGPRs, 3 waves) and take 12.4 now, a million
 // pairs of 3..7-gons 127 (52 bytes a lane spilled) and 120.5.
 template <int K, bool FIXED, bool ROWS>
 __global__ __launch_bounds__(prim_block<K>())
-__attribute__((amdgpu_waves_per_eu(4))) void k_intersect_fwd(IntersectArgs args) {
+__attribute__((amdgpu_waves_per_eu(K == 4 && FIXED ? 1 : 4))) void k_intersect_fwd(IntersectArgs args) {
   constexpr int BLOCK = prim_block<K>();
   constexpr int CAP = 2 * K;
   __shared__ __align__(16) float2 s_pt[CAP * BLOCK];
