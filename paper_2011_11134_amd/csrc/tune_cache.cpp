@@ -1,8 +1,8 @@
 // tune_cache.cpp -- the process-wide store of autotuned launch shapes and its
 // JSON file.  File format (UTF-8 JSON; unknown fields are ignored):
 //   {"format": "dgal-tune-cache", "version": 1,
-//    "entries": [{"key": "<arch>/<kind>/K4/fixed1/z1/seg1/b13.6",
-//                 "grid": 0, "cull_mult": 16, "exact_mult": 8, "bwd_mult": 0,
+//    "entries": [{"key": "<arch>/<kind>.<revision>/K4/fixed1/z1/seg1/b13.6",
+//                 "grid": 0, "cull_mult": 8, "exact_mult": 8, "bwd_mult": 0,
 //                 "tile_rows": 8, "ms": 0.25}, ...]}
 // A file that does not parse, or holds an entry outside the launchable
 // ranges, is refused whole.
